@@ -404,6 +404,14 @@ static int gathered_path(int32_t B) {
     return B <= kGemvMaxContexts ? 1 : 0;
 }
 
+// Dense product of rows with every context: the row-streaming kernel where it
+// takes the shape, else (more contexts, or a fixed DYNA_OPT_UNION_CFG) the
+// union kernel.
+static bool dense_rows_stream(const RowdotArgs& a) { return option_union_cfg() == 0 && row_stream_eligible(a); }
+static dyna_status launch_dense_rows(const RowdotArgs& a, hipStream_t s) {
+    return dense_rows_stream(a) ? launch_row_stream(a, s) : launch_union_gemm(a, s);
+}
+
 static dyna_status run_logits(const dyna_layout* L, const void* h, int32_t hdtype, int32_t B, int32_t k,
                               const int32_t* sel_sorted, const int32_t* sel_rowoff, float* logits,
                               int32_t cap, const Plan& plan, hipStream_t s) {
@@ -770,15 +778,8 @@ dyna_status draft_head_core(const dyna_router* r, const dyna_layout* L, const vo
     // union rows: one dense product of the union's slabs with every context
     // (it needs only one list entry per union cluster, and writes one shared
     // copy of the slots' vocabulary ids)
-    // A few rows over a short union take the per-chunk gathered kernel (one
-    // unit of every row per chunk, private rings per wave): measured at ten
-    // rows, 7 us faster per step than the dense union kernel at unions of
-    // 3.7-9.2k slots (row strides up to 39k) and 4 us slower at 32k.  A
-    // fixed union shape (DYNA_OPT_UNION_CFG) always takes the dense kernel.
-    constexpr int32_t kSmallUnionCap = 65536;
-    const bool small_union = option_union_cfg() == 0 && B <= 16 && cap <= kSmallUnionCap;
     const bool dense_union = union_mode && option_logits_path() == 0 && L->wdtype == DYNA_BF16 &&
-                             adtype == DYNA_BF16 && L->d % 8 == 0 && !small_union;
+                             adtype == DYNA_BF16 && L->d % 8 == 0;
     if (union_mode) {
         // per-row clusters, then one shared shortlist (its ids go to sel_sorted)
         TRY(launch_topk_clusters(c.scores, B, L->M, k, clusters, c.topk_scores, nullptr, nullptr, nullptr, nullptr,
@@ -817,7 +818,7 @@ dyna_status draft_head_core(const dyna_router* r, const dyna_layout* L, const vo
         want_sample ? out_sample_logprob : nullptr, c.select_ws, c.slot_vid);
     if (fused) return timed([&] { return launch_logits_greedy(a, sa, c.partials, c.counters, stream); }, stream);
     if (dense_union && !gather_lds_eligible(a)) return set_error(DYNA_ERR_UNSUPPORTED, "union: kernel arguments");
-    if (dense_union) TRY(timed([&] { return launch_union_gemm(a, stream); }, stream));
+    if (dense_union) TRY(timed([&] { return launch_dense_rows(a, stream); }, stream));
     else TRY(timed_rowdot(a, union_mode ? option_logits_path() : gathered_path(B), stream));
     // union rows over a few thousand slots select faster in one launch (one
     // workgroup per row); long union rows split into segments.  Measured at
@@ -977,10 +978,13 @@ DYNA_API dyna_status dyna_dense_head(const void* W, int32_t wdtype, int32_t n_ro
     if (option_logits_path() == 0 && B > 4 && wdtype == DYNA_BF16 && hdtype == DYNA_BF16) {
         // several contexts: the rows streamed once through LDS by the union
         // kernel, every context multiplied on the matrix cores
-        a.plan = plan;
-        a.max_chunks_bound = plan.max_chunks;
-        TRY(launch_full_plan(n_rows, B, plan, stream));
-        TRY(timed([&] { return launch_union_gemm(a, stream); }, stream));
+        if (!dense_rows_stream(a)) {
+            // the union kernel walks a plan
+            a.plan = plan;
+            a.max_chunks_bound = plan.max_chunks;
+            TRY(launch_full_plan(n_rows, B, plan, stream));
+        }
+        TRY(timed([&] { return launch_dense_rows(a, stream); }, stream));
     } else {
         TRY(timed_rowdot(a, option_logits_path(), stream));
     }

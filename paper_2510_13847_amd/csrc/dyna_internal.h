@@ -26,7 +26,7 @@ typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 struct Chunk {
     int32_t r0;        // first layout row
     int32_t nrows;     // rows in this chunk (1..kChunkRows)
-    int32_t list_off;  // first entry of the cluster's context list
+    int32_t list_off;  // first entry of the cluster's context list (compact plans: first row's output slot)
     int32_t list_cnt;  // number of contexts that selected the cluster
 };
 
@@ -146,12 +146,16 @@ dyna_status launch_dense_splitk(const RowdotArgs& a, float* part, size_t part_fl
 // through LDS (MFMA tiles)
 bool gather_lds_eligible(const RowdotArgs& a);
 dyna_status launch_gather_lds(const RowdotArgs& a, hipStream_t stream);
-// union rows (every plan chunk lists contexts 0..B-1 in order): dense
+// union rows (compact plan: every chunk stands for contexts 0..B-1): dense
 // LDS-staged MFMA product; vid_out gets one shared row [slots]
 dyna_status launch_union_gemm(const RowdotArgs& a, hipStream_t stream);
+// stream.hip: the same product for up to 64 contexts (bf16), over a compact
+// union plan or (plan.hdr == nullptr) the rows [0, n_rows)
+bool row_stream_eligible(const RowdotArgs& a);
+dyna_status launch_row_stream(const RowdotArgs& a, hipStream_t stream);
 // Plan over rows [0, V): one chunk per 16 rows, every chunk shared by all B
-// contexts (one list entry, slot base 0), so the union kernel computes the
-// dense product of the rows with every context.
+// contexts, so the union kernel computes the dense product of the rows with
+// every context.
 dyna_status launch_full_plan(int32_t V, int32_t B, const Plan& plan, hipStream_t stream);
 // The same product with an argmax epilogue: every plan row against the B
 // contexts (centroids); vid_out[slot] = the best context (ties to the lower

@@ -405,8 +405,8 @@ dyna_status launch_ring_cfg(const RowdotArgs& a, hipStream_t stream) {
 // own counter wait and one workgroup barrier; that barrier also frees the
 // stage read in the previous iteration, which the next load then fills.
 // Workgroups are persistent (tile blockIdx.x, + gridDim.x, ...), so the ring
-// runs on across tiles without refilling.  The plan lists one entry per union
-// cluster (its slot base); every chunk stands for all B contexts.
+// runs on across tiles without refilling.  A chunk's list_off is the output
+// slot of its first row; every chunk stands for all B contexts.
 template <int T>
 struct UnionCursor {
     int64_t tile;
@@ -414,7 +414,7 @@ struct UnionCursor {
     int kb;         // k block
     int r0[T];      // first layout row of each of this wave's chunks
     int nrows[T];   // their valid rows (0: no chunk)
-    int sb[T];      // slot base of each chunk's cluster
+    int sb[T];      // slot base of each chunk (slot of layout row 0)
 };
 
 template <int NW, int T>
@@ -435,7 +435,7 @@ __device__ __forceinline__ void union_set_tile(UnionCursor<T>& u, int64_t tile, 
             if (nr > 0 && lc > 0) {
                 u.r0[t] = r0;
                 u.nrows[t] = min(kMfmaRows, nr);
-                u.sb[t] = ((sptr<int32_t>)plan.list)[2 * (int64_t)lo + 1];
+                u.sb[t] = lo - r0;
             }
         }
     }

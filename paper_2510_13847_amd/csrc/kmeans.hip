@@ -82,16 +82,16 @@ __global__ void f32_to_bf16_kernel(const float* __restrict__ src, uint16_t* __re
         dst[i] = to_bf16_rne(src[i]);
 }
 
-// Plan over every row: chunk c is rows [16c, 16c + 16), and its one list
-// entry (slot base 0) stands for all B centroids.
+// Plan over every row: chunk c is rows [16c, 16c + 16), output slot = row,
+// and stands for all B centroids.
 __global__ void full_plan_kernel(int32_t V, int32_t B, Plan plan) {
     const int64_t n = ((int64_t)V + kChunkRows - 1) / kChunkRows;
     for (int64_t c = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; c < n; c += (int64_t)gridDim.x * blockDim.x)
-        plan.chunks[c] = Chunk{(int32_t)(c * kChunkRows), (int32_t)min<int64_t>(kChunkRows, V - c * kChunkRows), 0, B};
+        plan.chunks[c] = Chunk{(int32_t)(c * kChunkRows), (int32_t)min<int64_t>(kChunkRows, V - c * kChunkRows),
+                               (int32_t)(c * kChunkRows), B};
     if (blockIdx.x == 0 && threadIdx.x == 0) {
-        plan.list[0] = ListEntry{0, 0};
         plan.hdr->n_chunks = (int32_t)n;
-        plan.hdr->n_entries = 1;
+        plan.hdr->n_entries = 0;
     }
 }
 

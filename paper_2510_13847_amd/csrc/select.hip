@@ -275,8 +275,8 @@ __global__ __launch_bounds__(kPlanThreads) void plan_kernel(
 // every row (entries i * B .. i * B + B - 1 of the list for union cluster i).
 // Writes the plan, row_len[b] = |union| for every row, and the union itself
 // (ascending ids, -1 past its end) to sel_u[0 .. min(M, B * k)).
-// compact: the list holds one entry per union cluster (entry i, context 0)
-// and a chunk's count is still B; only the dense union kernel reads this form.
+// compact: no lists; a chunk's list_off is the shortlist slot of its first row
+// (the dense union kernels read this form).
 __global__ __launch_bounds__(kPlanThreads) void union_plan_kernel(
     const int32_t* __restrict__ offsets, int M, const int32_t* __restrict__ topk_ids, int B, int k,
     int32_t* __restrict__ row_len, int32_t* __restrict__ sel_u, int u_cap, Plan plan, int compact) {
@@ -356,20 +356,21 @@ __global__ __launch_bounds__(kPlanThreads) void union_plan_kernel(
             const int m = uid[i];
             const int ci = c - coff[i];
             const int o = offsets[m], n = offsets[m + 1] - o;
-            plan.chunks[c] = Chunk{o + ci * kChunkRows, min(kChunkRows, n - ci * kChunkRows), compact ? i : i * B, B};
+            plan.chunks[c] = Chunk{o + ci * kChunkRows, min(kChunkRows, n - ci * kChunkRows),
+                                   compact ? roff[i] + ci * kChunkRows : i * B, B};
         }
     }
-    // every row in every union cluster's list (compact: row 0 stands for all)
-    const int per = compact ? 1 : B;
-    for (int64_t e = t; e < (int64_t)U * per; e += kPlanThreads) {
-        const int i = (int)(e / per), b = (int)(e - (int64_t)i * per);
-        plan.list[e] = ListEntry{b, roff[i] - offsets[uid[i]]};
-    }
+    // every row in every union cluster's list
+    if (!compact)
+        for (int64_t e = t; e < (int64_t)U * B; e += kPlanThreads) {
+            const int i = (int)(e / B), b = (int)(e - (int64_t)i * B);
+            plan.list[e] = ListEntry{b, roff[i] - offsets[uid[i]]};
+        }
     for (int b = t; b < B; b += kPlanThreads) row_len[b] = len;
     for (int i = t; i < u_cap; i += kPlanThreads) sel_u[i] = i < U ? uid[i] : -1;
     if (t == 0) {
         plan.hdr->n_chunks = n_chunks;
-        plan.hdr->n_entries = U * per;
+        plan.hdr->n_entries = compact ? 0 : U * B;
     }
 }
 
