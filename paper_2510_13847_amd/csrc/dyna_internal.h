@@ -161,6 +161,10 @@ dyna_status launch_full_plan(int32_t V, int32_t B, const Plan& plan, hipStream_t
 // contexts (centroids); vid_out[slot] = the best context (ties to the lower
 // id), out[slot] = its product (out may be null).
 dyna_status launch_union_argmax(const RowdotArgs& a, int cfg, hipStream_t stream);
+// assign.hip: the same assignment for rows [0, V) on 256 x 256 tiles; keys
+// [V] is zero on entry and on return, score may be null.
+dyna_status launch_nearest_centroid(const void* W, int32_t V, int32_t d, const uint16_t* mu, int32_t M,
+                                    unsigned long long* keys, int32_t* assign, float* score, hipStream_t stream);
 // kmeans.hip: spherical k-means over the LM-head rows
 size_t kmeans_ws_bytes(int32_t V, int32_t d, int32_t M);
 dyna_status kmeans_assign(const void* W, int32_t V, int32_t d, const float* centroids, int32_t M,

@@ -7,8 +7,9 @@
 //    similarity.  Dividing a row by its norm does not change which centroid
 //    wins, so the raw bf16 rows are scored against the bf16 unit centroids:
 //    a dense V x M x d product on the matrix cores with an argmax epilogue
-//    (the union-row kernel, every row against every centroid), so no V x M
-//    score matrix is ever written.  Ties go to the lower centroid id.
+//    (assign.hip; the fixed DYNA_OPT_KMEANS_CFG shapes on the union-row
+//    kernel), so no V x M score matrix is ever written.  Ties go to the lower
+//    centroid id.
 //  * Update: a stable counting sort of the assignment (the layout's CSR
 //    kernels) lists each cluster's rows in ascending id; one workgroup per
 //    cluster sums its unit rows in that order in fp32 and divides by the
@@ -34,40 +35,32 @@ __device__ __forceinline__ uint16_t to_bf16_rne(float x) {
 __device__ __forceinline__ float bf16_lo(uint32_t w) { return __uint_as_float(w << 16); }
 __device__ __forceinline__ float bf16_hi(uint32_t w) { return __uint_as_float(w & 0xffff0000u); }
 
-// inv[v] = 1 / ||W[v]|| (0 for an all-zero row): one wave per row, 16-byte loads.
-__global__ __launch_bounds__(kKmThreads) void row_inv_norm_kernel(const uint16_t* __restrict__ W, int32_t V,
-                                                                  int32_t d, float* __restrict__ inv) {
-    const int lane = lane_id();
-    const int64_t v = (int64_t)blockIdx.x * (kKmThreads / kWave) + threadIdx.x / kWave;
-    if (v >= V) return;  // whole wave
-    const u32x4* row = reinterpret_cast<const u32x4*>(W + v * d);
-    float s = 0.0f;
-    for (int i = lane; i < d / 8; i += kWave) {
-        const u32x4 q = __builtin_nontemporal_load(row + i);
-#pragma unroll
-        for (int e = 0; e < 4; ++e) {
-            const float lo = bf16_lo(q[e]), hi = bf16_hi(q[e]);
-            s = fmaf(lo, lo, s);
-            s = fmaf(hi, hi, s);
-        }
-    }
-    s = wave_sum(s);
-    if (lane == 0) inv[v] = s > 0.0f ? 1.0f / sqrtf(s) : 0.0f;
-}
-
 // Centroid m starts at the unit row init_ids[m]; an id outside [0, V) gives a
-// zero centroid and sets *bad.
+// zero centroid and sets *bad.  Also clears the assignment's per-row maxima.
 __global__ __launch_bounds__(kKmThreads) void centroid_init_kernel(const uint16_t* __restrict__ W,
-                                                                   const float* __restrict__ inv,
                                                                    const int32_t* __restrict__ init_ids,
                                                                    int32_t V, int32_t d, float* __restrict__ mu32,
                                                                    uint16_t* __restrict__ mu16,
+                                                                   unsigned long long* __restrict__ keys,
                                                                    int32_t* __restrict__ bad) {
     const int64_t m = blockIdx.x;
+    for (int64_t i = m * kKmThreads + threadIdx.x; i < V; i += (int64_t)gridDim.x * kKmThreads) keys[i] = 0;
     const int32_t v = init_ids[m];
     const bool ok = v >= 0 && v < V;
     if (!ok && threadIdx.x == 0) atomicOr(bad, 1);
-    const float sc = ok ? inv[v] : 0.0f;
+    __shared__ float red[kKmThreads / kWave];
+    float ss = 0.0f;
+    for (int c = threadIdx.x; ok && c < d; c += kKmThreads) {
+        const float x = __uint_as_float((uint32_t)W[(int64_t)v * d + c] << 16);
+        ss = fmaf(x, x, ss);
+    }
+    ss = wave_sum(ss);
+    if (lane_id() == 0) red[threadIdx.x / kWave] = ss;
+    __syncthreads();
+    float tot = 0.0f;
+#pragma unroll
+    for (int w = 0; w < kKmThreads / kWave; ++w) tot += red[w];
+    const float sc = tot > 0.0f ? 1.0f / sqrtf(tot) : 0.0f;  // an all-zero row has no direction
     for (int c = threadIdx.x; c < d; c += kKmThreads) {
         const float x = ok ? __uint_as_float((uint32_t)W[(int64_t)v * d + c] << 16) * sc : 0.0f;
         mu32[m * d + c] = x;
@@ -77,9 +70,13 @@ __global__ __launch_bounds__(kKmThreads) void centroid_init_kernel(const uint16_
 
 __global__ void clear_word_kernel(int32_t* p) { *p = 0; }
 
-__global__ void f32_to_bf16_kernel(const float* __restrict__ src, uint16_t* __restrict__ dst, int64_t n) {
+// Also clears n_keys words of the assignment's per-row maxima.
+__global__ void f32_to_bf16_kernel(const float* __restrict__ src, uint16_t* __restrict__ dst, int64_t n,
+                                   unsigned long long* __restrict__ keys, int64_t n_keys) {
     for (int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; i < n; i += (int64_t)gridDim.x * blockDim.x)
         dst[i] = to_bf16_rne(src[i]);
+    for (int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; i < n_keys; i += (int64_t)gridDim.x * blockDim.x)
+        keys[i] = 0;
 }
 
 // Plan over every row: chunk c is rows [16c, 16c + 16), output slot = row,
@@ -97,15 +94,21 @@ __global__ void full_plan_kernel(int32_t V, int32_t B, Plan plan) {
 
 // mu[m] = (sum of the unit rows of cluster m, in ascending row id) / its norm;
 // an empty cluster or a zero sum keeps mu[m].  One workgroup per cluster;
-// thread t owns columns 8t + 2048 j, j < J.
+// thread t owns columns 8t + 2048 j, j < J.  The rows stream in batches of
+// kKmUnroll, the next batch in flight while the current one's norms are
+// summed across the workgroup (a pass of its own for the norms read every
+// row once more: 152 us over 128256 x 4096 rows, and this kernel takes 190 us
+// with them against 207 without).  Bound by HBM (5.5 TB/s); the register
+// bound lets four workgroups share a compute unit, so that 1024 clusters run
+// at once (1116 us per round against 1133 with three).
 template <int J>
-__global__ __launch_bounds__(kKmThreads) void centroid_update_kernel(const uint16_t* __restrict__ W,
-                                                                     const float* __restrict__ inv,
+__global__ __launch_bounds__(kKmThreads, (J <= 2 ? 4 : 2)) void centroid_update_kernel(const uint16_t* __restrict__ W,
                                                                      const int32_t* __restrict__ perm,
                                                                      const int32_t* __restrict__ offsets, int32_t d,
                                                                      float* __restrict__ mu32,
                                                                      uint16_t* __restrict__ mu16) {
-    __shared__ float red[kKmThreads / kWave];
+    constexpr int NW = kKmThreads / kWave;
+    __shared__ float red[2][NW][kKmUnroll];
     const int64_t m = blockIdx.x;
     const int32_t i0 = offsets[m], i1 = offsets[m + 1];
     if (i0 >= i1) return;  // empty: unchanged (whole workgroup)
@@ -114,44 +117,82 @@ __global__ __launch_bounds__(kKmThreads) void centroid_update_kernel(const uint1
     for (int j = 0; j < J; ++j)
 #pragma unroll
         for (int e = 0; e < 8; ++e) s[j][e] = 0.0f;
-    for (int32_t i = i0; i < i1; i += kKmUnroll) {
-        int64_t v[kKmUnroll];
-        float sc[kKmUnroll];
+    u32x4 x[kKmUnroll][J], y[kKmUnroll][J];
+    int32_t v[kKmUnroll];
+    // rows i .. i + kKmUnroll - 1 (past the cluster: zeros, which add nothing)
+    auto ids = [&](int32_t i) {
 #pragma unroll
-        for (int q = 0; q < kKmUnroll; ++q) {
-            const bool in = i + q < i1;
-            v[q] = perm[in ? i + q : i0];
-            sc[q] = in ? inv[v[q]] : 0.0f;  // a row past the cluster adds zeros
-        }
-        u32x4 x[kKmUnroll][J];
+        for (int q = 0; q < kKmUnroll; ++q) v[q] = i + q < i1 ? perm[i + q] : -1;
+    };
+    auto load = [&]() {
 #pragma unroll
         for (int q = 0; q < kKmUnroll; ++q)
 #pragma unroll
             for (int j = 0; j < J; ++j) {
                 const int c0 = 8 * (int)threadIdx.x + kKmCols * j;
-                x[q][j] = c0 < d ? *reinterpret_cast<const u32x4*>(W + v[q] * d + c0) : u32x4{0u, 0u, 0u, 0u};
+                y[q][j] = u32x4{0u, 0u, 0u, 0u};
+                if (v[q] >= 0 && c0 < d)
+                    y[q][j] = __builtin_nontemporal_load(reinterpret_cast<const u32x4*>(W + (int64_t)v[q] * d + c0));
             }
+    };
+    ids(i0);
+    load();
+    ids(i0 + kKmUnroll);
+    int at = 0;
+    for (int32_t i = i0; i < i1; i += kKmUnroll, at ^= 1) {
 #pragma unroll
         for (int q = 0; q < kKmUnroll; ++q)
+#pragma unroll
+            for (int j = 0; j < J; ++j) x[q][j] = y[q][j];
+        if (i + kKmUnroll < i1) {
+            load();
+            ids(i + 2 * kKmUnroll);
+        }
+        // the batch's squared norms (two places in turn: one barrier a batch)
+#pragma unroll
+        for (int q = 0; q < kKmUnroll; ++q) {
+            float n = 0.0f;
 #pragma unroll
             for (int j = 0; j < J; ++j)
 #pragma unroll
                 for (int e = 0; e < 4; ++e) {
-                    s[j][2 * e] = fmaf(bf16_lo(x[q][j][e]), sc[q], s[j][2 * e]);
-                    s[j][2 * e + 1] = fmaf(bf16_hi(x[q][j][e]), sc[q], s[j][2 * e + 1]);
+                    const float lo = bf16_lo(x[q][j][e]), hi = bf16_hi(x[q][j][e]);
+                    n = fmaf(lo, lo, n);
+                    n = fmaf(hi, hi, n);
                 }
+            n = wave_sum(n);
+            if (lane_id() == 0) red[at][threadIdx.x / kWave][q] = n;
+        }
+        // LDS only: the next batch's loads stay in flight
+        __builtin_amdgcn_s_waitcnt(0xC07F);
+        __asm__ __volatile__("s_barrier" ::: "memory");
+#pragma unroll
+        for (int q = 0; q < kKmUnroll; ++q) {
+            float n = 0.0f;
+#pragma unroll
+            for (int w = 0; w < NW; ++w) n += red[at][w][q];
+            const float sc = n > 0.0f ? 1.0f / sqrtf(n) : 0.0f;  // an all-zero row adds nothing
+#pragma unroll
+            for (int j = 0; j < J; ++j)
+#pragma unroll
+                for (int e = 0; e < 4; ++e) {
+                    s[j][2 * e] = fmaf(bf16_lo(x[q][j][e]), sc, s[j][2 * e]);
+                    s[j][2 * e + 1] = fmaf(bf16_hi(x[q][j][e]), sc, s[j][2 * e + 1]);
+                }
+        }
     }
+    __syncthreads();
     float ss = 0.0f;
 #pragma unroll
     for (int j = 0; j < J; ++j)
 #pragma unroll
         for (int e = 0; e < 8; ++e) ss = fmaf(s[j][e], s[j][e], ss);
     ss = wave_sum(ss);
-    if (lane_id() == 0) red[threadIdx.x / kWave] = ss;
+    if (lane_id() == 0) red[0][threadIdx.x / kWave][0] = ss;
     __syncthreads();
     float tot = 0.0f;
 #pragma unroll
-    for (int w = 0; w < kKmThreads / kWave; ++w) tot += red[w];
+    for (int w = 0; w < NW; ++w) tot += red[0][w][0];
     if (!(tot > 0.0f)) return;  // zero sum: unchanged
     const float rn = 1.0f / sqrtf(tot);
 #pragma unroll
@@ -172,13 +213,13 @@ size_t al256(size_t x) { return (x + 255) & ~size_t(255); }
 
 // Workspace views.
 struct KmWs {
-    float* inv;        // [V]
     uint16_t* mu16;    // [M, d]
     float* mu32;       // [M, d] (used when the caller keeps no centroids)
     int32_t* assign;   // [V] (used when the caller keeps no assignment)
     int32_t* perm;     // [V]
     int32_t* offsets;  // [M + 1]
     int32_t* bad;      // [1]
+    unsigned long long* keys;  // [V] the assignment's per-row maxima
     Plan plan;
     void* csr;         // layout_ws_bytes(V, M)
     size_t bytes;
@@ -194,13 +235,13 @@ KmWs km_carve(int32_t V, int32_t d, int32_t M, void* base) {
         return q;
     };
     const int64_t n_chunks = ((int64_t)V + kChunkRows - 1) / kChunkRows;
-    w.inv = static_cast<float*>(take(sizeof(float) * (size_t)V));
     w.mu16 = static_cast<uint16_t*>(take(sizeof(uint16_t) * (size_t)M * d));
     w.mu32 = static_cast<float*>(take(sizeof(float) * (size_t)M * d));
     w.assign = static_cast<int32_t*>(take(sizeof(int32_t) * (size_t)V));
     w.perm = static_cast<int32_t*>(take(sizeof(int32_t) * (size_t)V));
     w.offsets = static_cast<int32_t*>(take(sizeof(int32_t) * ((size_t)M + 1)));
     w.bad = static_cast<int32_t*>(take(sizeof(int32_t)));
+    w.keys = static_cast<unsigned long long*>(take(sizeof(unsigned long long) * (size_t)V));
     w.plan.hdr = static_cast<PlanHeader*>(take(sizeof(PlanHeader)));
     w.plan.chunks = static_cast<Chunk*>(take(sizeof(Chunk) * (size_t)n_chunks));
     w.plan.list = static_cast<ListEntry*>(take(sizeof(ListEntry)));
@@ -211,14 +252,11 @@ KmWs km_carve(int32_t V, int32_t d, int32_t M, void* base) {
     return w;
 }
 
-dyna_status launch_inv_norms(const uint16_t* W, int32_t V, int32_t d, float* inv, hipStream_t stream) {
-    const int64_t blocks = ((int64_t)V + kKmThreads / kWave - 1) / (kKmThreads / kWave);
-    row_inv_norm_kernel<<<(unsigned)blocks, kKmThreads, 0, stream>>>(W, V, d, inv);
-    return check_launch("row_inv_norm_kernel");
-}
-
+// w.keys is zero on entry and on return.
 dyna_status launch_assign(const uint16_t* W, int32_t V, int32_t d, const uint16_t* mu16, int32_t M, int32_t* assign,
-                          float* score, const Plan& plan, hipStream_t stream) {
+                          float* score, const KmWs& w, hipStream_t stream) {
+    if (option_kmeans_cfg() == 0) return launch_nearest_centroid(W, V, d, mu16, M, w.keys, assign, score, stream);
+    if (dyna_status s = launch_full_plan(V, M, w.plan, stream); s != DYNA_OK) return s;
     RowdotArgs a{};
     a.W = W;
     a.wdtype = DYNA_BF16;
@@ -229,8 +267,8 @@ dyna_status launch_assign(const uint16_t* W, int32_t V, int32_t d, const uint16_
     a.out = score;
     a.ld = 0;
     a.act = DYNA_ACT_NONE;
-    a.plan = plan;
-    a.max_chunks_bound = plan.max_chunks;
+    a.plan = w.plan;
+    a.max_chunks_bound = w.plan.max_chunks;
     a.vid_out = assign;
     return launch_union_argmax(a, option_kmeans_cfg(), stream);
 }
@@ -241,7 +279,7 @@ dyna_status launch_update(const uint16_t* W, int32_t V, int32_t d, const int32_t
     const int J = (d + kKmCols - 1) / kKmCols;
 #define DYNA_KM_UPD(NJ)                                                                                       \
     if (J <= NJ) {                                                                                            \
-        centroid_update_kernel<NJ><<<M, kKmThreads, 0, stream>>>(W, w.inv, w.perm, w.offsets, d, mu32, w.mu16); \
+        centroid_update_kernel<NJ><<<M, kKmThreads, 0, stream>>>(W, w.perm, w.offsets, d, mu32, w.mu16); \
         return check_launch("centroid_update_kernel");                                                        \
     }
     DYNA_KM_UPD(1)
@@ -266,20 +304,20 @@ dyna_status kmeans_assign(const void* W, int32_t V, int32_t d, const float* cent
                           int32_t* out_assign, float* out_score, void* ws, hipStream_t stream) {
     const KmWs w = km_carve(V, d, M, ws);
     const int64_t n = (int64_t)M * d;
-    f32_to_bf16_kernel<<<(unsigned)std::min<int64_t>(4096, (n + 255) / 256), 256, 0, stream>>>(centroids, w.mu16, n);
+    f32_to_bf16_kernel<<<(unsigned)std::min<int64_t>(4096, (n + 255) / 256), 256, 0, stream>>>(centroids, w.mu16, n,
+                                                                                         w.keys, V);
     if (dyna_status s = check_launch("f32_to_bf16_kernel"); s != DYNA_OK) return s;
-    if (dyna_status s = launch_full_plan(V, M, w.plan, stream); s != DYNA_OK) return s;
-    return launch_assign(static_cast<const uint16_t*>(W), V, d, w.mu16, M, out_assign, out_score, w.plan, stream);
+    return launch_assign(static_cast<const uint16_t*>(W), V, d, w.mu16, M, out_assign, out_score, w, stream);
 }
 
 dyna_status kmeans_update(const void* W, int32_t V, int32_t d, const int32_t* assign, int32_t M, float* centroids,
                           void* ws, hipStream_t stream) {
     const KmWs w = km_carve(V, d, M, ws);
     const uint16_t* Wb = static_cast<const uint16_t*>(W);
-    if (dyna_status s = launch_inv_norms(Wb, V, d, w.inv, stream); s != DYNA_OK) return s;
     const int64_t n = (int64_t)M * d;
     // the bf16 copy of kept (empty-cluster) centroids stays consistent
-    f32_to_bf16_kernel<<<(unsigned)std::min<int64_t>(4096, (n + 255) / 256), 256, 0, stream>>>(centroids, w.mu16, n);
+    f32_to_bf16_kernel<<<(unsigned)std::min<int64_t>(4096, (n + 255) / 256), 256, 0, stream>>>(centroids, w.mu16, n,
+                                                                                         nullptr, 0);
     if (dyna_status s = check_launch("f32_to_bf16_kernel"); s != DYNA_OK) return s;
     return launch_update(Wb, V, d, assign, M, w, centroids, stream);
 }
@@ -290,13 +328,11 @@ dyna_status kmeans_run(const void* W, int32_t V, int32_t d, int32_t M, const int
     const uint16_t* Wb = static_cast<const uint16_t*>(W);
     float* mu32 = out_centroids ? out_centroids : w.mu32;
     int32_t* assign = out_cluster_of ? out_cluster_of : w.assign;
-    if (dyna_status s = launch_inv_norms(Wb, V, d, w.inv, stream); s != DYNA_OK) return s;
     clear_word_kernel<<<1, 1, 0, stream>>>(w.bad);
-    centroid_init_kernel<<<M, kKmThreads, 0, stream>>>(Wb, w.inv, init_ids, V, d, mu32, w.mu16, w.bad);
+    centroid_init_kernel<<<M, kKmThreads, 0, stream>>>(Wb, init_ids, V, d, mu32, w.mu16, w.keys, w.bad);
     if (dyna_status s = check_launch("centroid_init_kernel"); s != DYNA_OK) return s;
-    if (dyna_status s = launch_full_plan(V, M, w.plan, stream); s != DYNA_OK) return s;
     for (int32_t it = 0; it < iters; ++it) {
-        if (dyna_status s = launch_assign(Wb, V, d, w.mu16, M, assign, nullptr, w.plan, stream); s != DYNA_OK)
+        if (dyna_status s = launch_assign(Wb, V, d, w.mu16, M, assign, nullptr, w, stream); s != DYNA_OK)
             return s;
         if (dyna_status s = launch_update(Wb, V, d, assign, M, w, mu32, stream); s != DYNA_OK) return s;
     }

@@ -126,7 +126,7 @@ __global__ __launch_bounds__(kStreamThreads, (StreamShape<NKS, SS, NG>::EU)) voi
     const int half = SS == 1 ? k1 - k0 : (k1 - k0 + 1) / 2;
     const int lsub = lane / Sh::PIECES, lpc = lane % Sh::PIECES;
     const int col = lane & 15, kq = lane >> 4;
-    // byte offset of this lane's piece of each stage inside a tile; a lane
+    // byte offset of this lane's piece of each stage inside a row; a lane
     // without one (past the wave's share or past K) has an offset beyond the
     // buffer, whose loads give zero
     uint32_t voff[SS];
@@ -134,18 +134,20 @@ __global__ __launch_bounds__(kStreamThreads, (StreamShape<NKS, SS, NG>::EU)) voi
     for (int s = 0; s < SS; ++s) {
         const int b = s == 0 ? k0 : k0 + half, e = s == 0 ? k0 + half : k1;
         const int c = b * 32 + lpc * 8;
-        voff[s] = c < min(K, e * 32) ? 2u * (uint32_t)(lsub * K + c) : 0x80000000u;
+        voff[s] = c < min(K, e * 32) ? 2u * (uint32_t)c : 0x80000000u;
     }
 
-    // load i of a tile's stage s; rows past the tile's end are beyond the
-    // buffer too
+    // load i of a tile's stage s; rows past the tile's end repeat its last row
+    // and only reach products that are not stored
     auto tile_rsrc = [&](const StreamTile& t) {
         return __builtin_amdgcn_make_buffer_rsrc(const_cast<uint16_t*>(W) + (int64_t)t.r0 * K, (short)0,
                                                  t.nrows * K * 2, 0x00027000);
     };
     auto load = [&](__amdgpu_buffer_rsrc_t rsrc, int nrows, int s, int i) -> u32x4 {
-        const int row = Sh::RPI == 1 ? min(i, nrows - 1) : Sh::RPI * i;
-        return __builtin_amdgcn_raw_buffer_load_b128(rsrc, (int)voff[s], row * K * 2, kPolicy);
+        if constexpr (Sh::RPI == 1)
+            return __builtin_amdgcn_raw_buffer_load_b128(rsrc, (int)voff[s], min(i, nrows - 1) * K * 2, kPolicy);
+        const uint32_t row = (uint32_t)min(Sh::RPI * i + lsub, nrows - 1);
+        return __builtin_amdgcn_raw_buffer_load_b128(rsrc, (int)(voff[s] + row * (uint32_t)(K * 2)), 0, kPolicy);
     };
     u32x4 A[Sh::NA];
 
