@@ -492,13 +492,13 @@ __global__ __launch_bounds__(kNT) void select_partial_kernel(SelectArgs a) {
         zv[q] = q < n ? canon(zr[q]) : -__builtin_inff();
         list[q] = q < n ? sel_key(zv[q], vid[q]) : 0;
     }
-    // the segment's k_t best keys by radix selection (measured faster than
-    // per-thread sorted lists merged in k_t wave rounds: 4 us per union step
-    // of 64 rows, 3.5 us per dense head)
+    // the segment's k_t best keys
     {
         __shared__ int rhist[256];
-        __shared__ uint64_t rsel[DYNA_MAX_KT];
-        block_radix_topk<kNT, kPer>(list, a.k_t, min(kSegLen, len - seg0), rhist, rsel, top);
+        __shared__ uint64_t rsel[kBoundKeys];
+        const int n_seg = min(kSegLen, len - seg0);
+        if (a.k_t > 16 || !block_bound_topk<kNT, kPer>(list, a.k_t, rsel, top))
+            block_radix_topk<kNT, kPer>(list, a.k_t, n_seg, rhist, rsel, top);
     }
     // segment max = value of the best key (or -inf for an empty segment)
     const float smax = top[0] != 0 ? key_val(top[0]) : -__builtin_inff();

@@ -170,7 +170,7 @@ __device__ void block_topk_rounds(uint64_t (&list)[L], int k_t, uint64_t* cand /
 // the prefix are exactly the ones still needed.  The selected keys, sorted
 // descending, go to out[0..k_t); missing ones (short rows) are 0.
 template <int NT, int P>
-__device__ void block_radix_topk(const uint64_t (&kk)[P], int k_t, int n_valid, int* hist /* LDS [256] */,
+__device__ __forceinline__ void block_radix_topk(const uint64_t (&kk)[P], int k_t, int n_valid, int* hist /* LDS [256] */,
                                  uint64_t* sel /* LDS [k_t] */, uint64_t* out /* LDS [k_t] */) {
     __shared__ uint64_t sh_prefix;
     __shared__ int sh_need, sh_done, sh_n;
@@ -243,6 +243,81 @@ __device__ void block_radix_topk(const uint64_t (&kk)[P], int k_t, int n_valid, 
     __syncthreads();
 }
 
+// Exact top-k_t (k_t <= 16) of per-thread keys held in registers (P per
+// thread, 0 = empty; valid keys are distinct and nonzero).  The keys fall
+// into 16 groups by lane % 16; the k_t-th largest group maximum is a bound
+// that k_t keys reach, and few others do (16-45 in all on random rows; slots
+// next to each other lie in different groups, so a run of large logits does
+// not crowd one).  Those are collected in LDS and ranked by counting: three
+// barriers where the radix selection takes four per byte, whose counters the
+// crowded exponent bytes also serialise.  Its keys need no second buffer, so
+// rows of up to 16 slots per thread qualify (ten rows of 9.2k slots: 19 us
+// with per-thread sorted lists, 8 now).  False (for the
+// whole workgroup, nothing written) when more than kBoundKeys keys reach the
+// bound.
+constexpr int kBoundKeys = 256;
+template <int NT, int P>
+__device__ __forceinline__ bool block_bound_topk(const uint64_t (&kk)[P], int k_t,
+                                                 uint64_t* sel /* LDS [kBoundKeys] */, uint64_t* out /* LDS [k_t] */) {
+    constexpr int NW = NT / kWave;
+    __shared__ uint64_t group_max[NW][16];
+    __shared__ int sh_count;
+    const int lane = lane_id(), w = threadIdx.x / kWave;
+    uint64_t m = kk[0];
+#pragma unroll
+    for (int q = 1; q < P; ++q) m = kk[q] > m ? kk[q] : m;
+#pragma unroll
+    for (int step = 16; step <= 32; step <<= 1) {
+        const int src = (lane ^ step) << 2;
+        const uint32_t lo = (uint32_t)__builtin_amdgcn_ds_bpermute(src, (int)(uint32_t)m);
+        const uint32_t hi = (uint32_t)__builtin_amdgcn_ds_bpermute(src, (int)(uint32_t)(m >> 32));
+        const uint64_t y = ((uint64_t)hi << 32) | lo;
+        m = y > m ? y : m;
+    }
+    if (lane < 16) group_max[w][lane] = m;
+    if (threadIdx.x == 0) sh_count = 0;
+    __syncthreads();
+    // every wave for itself: lane l holds the maximum of group l % 16
+    uint64_t g = 0;
+#pragma unroll
+    for (int q = 0; q < NW; ++q) {
+        const uint64_t y = group_max[q][lane & 15];
+        g = y > g ? y : g;
+    }
+    int rank = 0;
+#pragma unroll
+    for (int j = 0; j < 16; ++j) {
+        const uint32_t lo = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)g, j);
+        const uint32_t hi = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)(g >> 32), j);
+        const uint64_t y = ((uint64_t)hi << 32) | lo;
+        rank += y > g || (y == g && j < (lane & 15));  // (empty groups are all 0)
+    }
+    const int at = __builtin_ctzll(__ballot(rank == k_t - 1 && lane < 16));
+    const uint64_t bound = ((uint64_t)(uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)(g >> 32), at) << 32) |
+                           (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)g, at);
+#pragma unroll
+    for (int q = 0; q < P; ++q)
+        if (kk[q] != 0 && kk[q] >= bound) {
+            const int i = atomicAdd(&sh_count, 1);
+            if (i < kBoundKeys) sel[i] = kk[q];
+        }
+    __syncthreads();
+    const int n = sh_count;
+    if (n > kBoundKeys) return false;  // uniform
+    for (int i = threadIdx.x; i < max(n, k_t); i += NT) {
+        if (i >= n) {
+            out[i] = 0;  // a row of fewer than k_t keys
+            continue;
+        }
+        const uint64_t key = sel[i];
+        int r = 0;
+        for (int j = 0; j < n; ++j) r += sel[j] > key;
+        if (r < k_t) out[r] = key;
+    }
+    __syncthreads();
+    return true;
+}
+
 // Whole-row selection in one workgroup (shortlist-sized rows, k_t <= KT).
 // Max, top-k_t and the softmax sum read the row with coalesced strided loads;
 // only the sampling walk uses contiguous per-thread ranges, so that the CDF
@@ -253,7 +328,7 @@ constexpr int kRowTable = 1024;  // clusters per row the LDS table holds
 constexpr int kRowThreads = 1024;  // threads per row: a few slots each
 
 template <int KT, int NT>
-__device__ void select_row(const SelectArgs& a, int b) {
+__device__ __forceinline__ void select_row(const SelectArgs& a, int b) {
     __shared__ uint64_t cand[NT / kWave * KT];
     __shared__ uint64_t top[KT];
     __shared__ float red[2 * (NT / kWave) + 1];
@@ -285,18 +360,40 @@ __device__ void select_row(const SelectArgs& a, int b) {
         return (uint32_t)a.perm[t_base[lo] + j];
     };
 
-    constexpr int kRegPer = 8;  // rows up to NT * kRegPer slots keep their keys in registers
-    if (KT > 1 && len <= NT * kRegPer) {
-        __shared__ int rhist[256];
-        __shared__ uint64_t rsel[KT];
-        uint64_t kk[kRegPer];
+    // Top-k_t of a row of up to NT * P slots: its keys stay in registers, and
+    // where no sample is drawn the softmax mass is summed from them.
+    float tsum = 0.0f;
+    bool chosen = false, summed = false;
+    const bool sampling = a.uniforms != nullptr && a.out_sample != nullptr;
+    __shared__ int rhist[KT > 1 ? 256 : 1];
+    __shared__ uint64_t rsel[KT > 1 ? kBoundKeys : 1];
+    auto in_registers = [&](auto per) __attribute__((always_inline)) {
+        constexpr int P = decltype(per)::value;
+        uint64_t kk[P];
 #pragma unroll
-        for (int q = 0; q < kRegPer; ++q) {
+        for (int q = 0; q < P; ++q) {
             const int j = q * NT + threadIdx.x;
             kk[q] = j < len ? sel_key(canon(z[j]), vid_of(j)) : 0;
         }
-        block_radix_topk<NT, kRegPer>(kk, a.k_t, len, rhist, rsel, top);
-    } else {
+        if (!block_bound_topk<NT, P>(kk, a.k_t, rsel, top)) {
+            if constexpr (P <= 8) block_radix_topk<NT, P>(kk, a.k_t, len, rhist, rsel, top);
+            else return;  // (its registers do not hold 16 keys as well)
+        }
+        chosen = true;
+        const float mx = top[0] != 0 ? key_val(top[0]) : -__builtin_inff();
+        if (!sampling && mx != -__builtin_inff()) {
+#pragma unroll
+            for (int q = 0; q < P; ++q)
+                if (kk[q] != 0) tsum += expf((key_val(kk[q]) - mx) * a.inv_t);
+        }
+        summed = !sampling;
+    };
+    if constexpr (KT > 1) {
+        if (len <= NT * 4) in_registers(std::integral_constant<int, 4>{});
+        else if (len <= NT * 8) in_registers(std::integral_constant<int, 8>{});
+        else if (len <= NT * 16) in_registers(std::integral_constant<int, 16>{});
+    }
+    if (!chosen) {  // uniform
         uint64_t list[KT];
 #pragma unroll
         for (int q = 0; q < KT; ++q) list[q] = 0;
@@ -330,15 +427,13 @@ __device__ void select_row(const SelectArgs& a, int b) {
         block_topk_rounds<KT, NT, KT>(list, a.k_t, cand, top);
     }
     const float mx = top[0] != 0 ? key_val(top[0]) : -__builtin_inff();
-    const bool sampling = a.uniforms != nullptr && a.out_sample != nullptr;
 
     // softmax mass: strided when only top-k is asked, contiguous ranges
     // (shortlist order) when a sample must be drawn from the same sums
     const int E = (len + NT - 1) / NT;
     const int j0 = min(len, (int)threadIdx.x * E);
     const int j1 = min(len, j0 + E);
-    float tsum = 0.0f;
-    if (mx != -__builtin_inff()) {
+    if (!summed && mx != -__builtin_inff()) {
         if (sampling) {
             for (int j = j0; j < j1; ++j) tsum += expf((canon(z[j]) - mx) * a.inv_t);
         } else {

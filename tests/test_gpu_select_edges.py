@@ -1,0 +1,63 @@
+"""Top-k_t selection of one row at the edges of its register blocks (4096, 8192
+and 16384 slots), with logits that crowd the bound it selects by."""
+from __future__ import annotations
+
+import numpy as np
+import pytest
+
+torch = pytest.importorskip("torch")
+pytestmark = pytest.mark.gpu
+
+from paper_2510_13847_amd import dynahead as D  # noqa: E402
+
+DEV = "cuda"
+SIZES = [3, 17, 4096, 4097, 8192, 8193, 16384, 16385]
+
+
+@pytest.fixture(scope="module")
+def layout():
+    of = np.repeat(np.arange(len(SIZES), dtype=np.int32), SIZES)
+    of = of[np.random.default_rng(1).permutation(len(of))]
+    W = torch.zeros((len(of), 8), dtype=torch.bfloat16, device=DEV)
+    return D.build_layout(torch.from_numpy(of).to(DEV), W, len(SIZES))
+
+
+def _logits(kind, n, rng):
+    z = rng.standard_normal(n).astype(np.float32)
+    if kind == "equal":  # every key reaches the bound
+        z[:] = 0.25
+    elif kind == "runs":  # large values side by side, then equal ones
+        z[n // 3:n // 3 + 40] += 20
+        z[n // 2:n // 2 + 300] = 9.0
+    elif kind == "lanes":  # only every sixteenth slot is finite
+        z[np.arange(n) % 16 != 5] = -np.inf
+    elif kind == "special":
+        z[::3], z[1::7] = np.nan, -np.inf
+        z[n // 2] = np.inf
+    elif kind == "lowest":
+        z[:] = np.finfo(np.float32).min
+    return z
+
+
+@pytest.mark.parametrize("kind", ["random", "equal", "runs", "lanes", "special", "lowest"])
+@pytest.mark.parametrize("k_t", [1, 2, 10, 16])
+def test_top_kt(layout, kind, k_t):
+    rng = np.random.default_rng(k_t)
+    B = len(SIZES)
+    sel, off, length, ids = D.shortlist(layout, torch.arange(B, dtype=torch.int32, device=DEV)[:, None])
+    vids, cap = ids.cpu().numpy(), layout.cap(1)
+    z = np.full((B, cap), np.nan, np.float32)
+    for b, n in enumerate(SIZES):
+        z[b, :n] = _logits(kind, n, rng)
+    out = D.draft_select(layout, torch.from_numpy(z).to(DEV), sel, off, length, mode=D.SEL_TOPK, k_t=k_t)
+    got, lp = out["ids"].cpu().numpy(), out["logprobs"].cpu().numpy()
+    for b, n in enumerate(SIZES):
+        zz = np.where(np.isnan(z[b, :n]), -np.inf, z[b, :n]).astype(np.float64)
+        order = np.lexsort((vids[b, :n], -zz))[:k_t]
+        assert got[b, :len(order)].tolist() == vids[b, order].tolist()
+        assert (got[b, len(order):] == -1).all()
+        if np.isfinite(zz.max()):
+            ref = zz[order] - zz.max() - np.log(np.exp(zz - zz.max()).sum())
+            fin = np.isfinite(ref)
+            # fp32: the exponentials' sum over at most 16385 terms in blocks of 16, and one logarithm
+            assert np.abs(lp[b, :len(order)][fin] - ref[fin]).max() <= 1e-5 * max(1.0, np.abs(ref[fin]).max())
