@@ -22,9 +22,10 @@
 //      non-temporal 16-byte loads and dotted with h (in registers);
 //   5. each workgroup publishes its greedy partial; workgroup 0 polls them,
 //      merges them in workgroup order and writes the token, and the last
-//      workgroup writes the selection outputs.  For top-k_t (k_t <= 16) a
-//      partial also carries the workgroup's k_t best keys, and workgroup 0
-//      takes the k_t best of all of them.
+//      workgroup writes the selection outputs.  For top-k_t (k_t <= 16)
+//      over up to 16384 slots the waves hand over the logits themselves and
+//      workgroup 0 selects from them; beyond, a partial also carries the
+//      workgroup's k_t best keys, and workgroup 0 takes the k_t best of all.
 //
 // Hand-off protocol: every handed-off word is 64 bits, a 32-bit epoch tag
 // above the 32-bit value, written with one device-coherent store; readers
@@ -567,7 +568,7 @@ __device__ __forceinline__ void chain_outputs(const ChainArgs& A, const float* s
 // merges the softmax pairs in a fixed order; the last workgroup writes the
 // selection outputs.
 template <int NT>
-__device__ void chain_topk_finish(const ChainArgs& A, const GreedyState& st, uint64_t wk, bool bad, uint32_t e,
+__device__ __forceinline__ void chain_topk_finish(const ChainArgs& A, const GreedyState& st, uint64_t wk, bool bad, uint32_t e,
                                   int G, const float* sv, const int32_t* sid, const uint64_t* mkey,
                                   const int32_t* rowoff, int k, int L) {
     constexpr int NW = NT / kWave;
@@ -673,6 +674,171 @@ __device__ void chain_topk_finish(const ChainArgs& A, const GreedyState& st, uin
         if (A.out_logprobs)
             A.out_logprobs[r] = key != 0 ? (key_val(key) - f_m) * A.inv_t - logf(f_s) + lshift : -__builtin_inff();
     }
+}
+
+// Stage 5 of the top-k_t step over up to kChainLogits shortlist slots: every
+// wave has handed over its logits themselves (one tagged word per slot, in
+// the partials' place), and workgroup 0 polls all of them at once and selects
+// from its registers.  One round trip of 8 bytes per slot takes the place of
+// the key lists that every wave kept and every workgroup ranked and
+// published (33 words each), and of workgroup 0's merge of 256 lists.  The
+// selection is that of the row selection: the k_t-th largest of 16 group
+// maxima bounds the k_t-th value, and the few slots that reach it are ranked
+// by their (value, vocabulary id) keys.  Measured at 64 clusters, 8.0k slots
+// and k_t = 10, with the beam expansion: 37.1 -> 35.5 us (most of what is left is
+// workgroup 0 reading 64 KiB of coherent words).
+constexpr int kChainLogits = 16384;
+constexpr int kChainStatus = kChainMaxGrid;  // words ahead of the logits: one status per workgroup
+static_assert(kChainStatus + kChainLogits <= kPartWordsTopk * kChainMaxGrid, "the logits take the partials' place");
+
+template <int NT, int P>
+__device__ __forceinline__ void chain_logits_select(const ChainArgs& A, uint32_t e, int G, const int32_t* rowoff,
+                                                    const int32_t* sbase, int k, int L) {
+    constexpr int NW = NT / kWave;
+    constexpr int kKeys = 256;
+    static_assert(NT == kKeys, "one candidate per thread");
+    __shared__ uint32_t group_max[NW][16];
+    __shared__ uint64_t sel[kKeys];
+    __shared__ uint64_t s_top[kChainTopkMax], s_best[NW];
+    __shared__ float s_sum[NW];
+    __shared__ int s_n, s_bad;
+    const int t = threadIdx.x, lane = lane_id(), w = t / kWave;
+    const int kt = A.k_t;
+    if (t == 0) s_n = s_bad = 0;
+    if (t < kt) s_top[t] = 0;
+    uint32_t raw[P];
+    bool fail = false;
+    constexpr int kFlight = 16;  // words of a thread polled together (32 gain nothing, and cost the second
+                                 // workgroup per compute unit its registers)
+#pragma unroll
+    for (int q0 = 0; q0 < P; q0 += kFlight) {
+        uint32_t part[kFlight];
+        fail |= poll_own<NT, kFlight>(A, A.tpart + kChainStatus + NT * q0, L - NT * q0, e, part);
+#pragma unroll
+        for (int q = 0; q < kFlight; ++q) raw[q0 + q] = part[q];
+    }
+    for (int g0 = 0; g0 < G; g0 += NT) {
+        uint32_t st[1];
+        fail |= poll_own<NT, 1>(A, A.tpart + g0, G - g0, e, st);
+        fail |= g0 + t < G && st[0] != 0;
+    }
+    const uint32_t err_word = load_coherent(A.err);
+    // value codes (0: no slot)
+    uint32_t m = 0;
+#pragma unroll
+    for (int q = 0; q < P; ++q) {
+        raw[q] = t + NT * q < L ? ord_f32(__uint_as_float(raw[q])) : 0u;
+        m = raw[q] > m ? raw[q] : m;
+    }
+#pragma unroll
+    for (int step = 16; step <= 32; step <<= 1) {
+        const uint32_t y = (uint32_t)__builtin_amdgcn_ds_bpermute((lane ^ step) << 2, (int)m);
+        m = y > m ? y : m;
+    }
+    if (lane < 16) group_max[w][lane] = m;
+    __syncthreads();
+    if (fail) s_bad = 1;
+    uint32_t g = 0;
+#pragma unroll
+    for (int q = 0; q < NW; ++q) g = max(g, group_max[q][lane & 15]);
+    int rank = 0;
+    uint32_t best = 0;
+#pragma unroll
+    for (int j = 0; j < 16; ++j) {
+        const uint32_t y = (uint32_t)__builtin_amdgcn_readlane((int)g, j);
+        best = max(best, y);
+        rank += y > g || (y == g && j < (lane & 15));
+    }
+    const uint32_t bound =
+        (uint32_t)__builtin_amdgcn_readlane((int)g, __builtin_ctzll(__ballot(rank == kt - 1 && lane < 16)));
+    // softmax mass, and the slots that reach the bound
+    const float mx = best != 0 ? ord_to_f32(best) : -__builtin_inff();
+    float sum = 0.0f;
+#pragma unroll
+    for (int q = 0; q < P; ++q) {
+        if (raw[q] == 0) continue;
+        if (mx != -__builtin_inff()) sum += expf((ord_to_f32(raw[q]) - mx) * A.inv_t);
+        if (raw[q] >= bound) {
+            const int i = atomicAdd(&s_n, 1);
+            if (i < kKeys) sel[i] = ((uint64_t)raw[q] << 32) | (uint32_t)(t + NT * q);
+        }
+    }
+    sum = wave_sum(sum);
+    if (lane == 0) s_sum[w] = sum;
+    __syncthreads();
+    // a slot's (value, vocabulary id) key
+    auto key_of = [&](uint32_t code, int slot) -> uint64_t {
+        int lo = 0, hi = k - 1;  // the first cluster whose slab ends past the slot
+        while (lo < hi) {
+            const int mid = (lo + hi) >> 1;
+            if (rowoff[mid + 1] > slot) hi = mid;
+            else lo = mid + 1;
+        }
+        const uint32_t vid = (uint32_t)A.perm[(int64_t)sbase[lo] + (slot - rowoff[lo])];
+        return ((uint64_t)code << 32) | (0xffffffffu - vid);
+    };
+    const int n = s_n;
+    if (n <= kKeys) {  // uniform
+        const uint64_t mine = t < n ? key_of((uint32_t)(sel[t] >> 32), (int)(uint32_t)sel[t]) : 0;
+        __syncthreads();
+        sel[t] = mine;
+        __syncthreads();
+        if (mine != 0) {
+            int r = 0;
+            for (int j = 0; j < n; ++j) r += sel[j] > mine;
+            if (r < kt) s_top[r] = mine;
+        }
+    } else {
+        // long runs of equal logits: k_t rounds of a maximum below the last
+        uint64_t last = ~0ull;
+        for (int r = 0; r < kt; ++r) {
+            uint64_t b = 0;
+            for (int slot = t; slot < L; slot += NT) {  // (read again: the registers are not indexable)
+                const uint32_t code =
+                    ord_f32(__uint_as_float((uint32_t)load_coherent(A.tpart + kChainStatus + slot)));
+                if (code < bound) continue;
+                const uint64_t key = key_of(code, slot);
+                if (key < last && key > b) b = key;
+            }
+            b = wave_max_u64(b);
+            if (lane == 0) s_best[w] = b;
+            __syncthreads();
+            b = s_best[0];
+#pragma unroll
+            for (int q = 1; q < NW; ++q) b = s_best[q] > b ? s_best[q] : b;
+            if (t == 0) s_top[r] = b;
+            last = b;
+            __syncthreads();
+        }
+    }
+    float total = 0.0f;
+#pragma unroll
+    for (int q = 0; q < NW; ++q) total += s_sum[q];
+    __syncthreads();
+    const bool err = s_bad != 0 || err_word == e;
+    // every workgroup has read the epoch (its status carries it)
+    if (t == 0) store_coherent(A.epoch, e);
+    const float lshift = (A.beta > 0.0f && (int64_t)A.V > L) ? log1pf(-A.beta) : 0.0f;
+    if (t < kt) {
+        const uint64_t key = err ? 0 : s_top[t];
+        A.out_ids[t] = key != 0 ? (int32_t)key_id(key) : -1;
+        if (A.out_logprobs)
+            A.out_logprobs[t] = key != 0 ? (key_val(key) - mx) * A.inv_t - logf(total) + lshift : -__builtin_inff();
+    }
+}
+
+template <int NT>
+__device__ __forceinline__ void chain_logits_finish(const ChainArgs& A, bool bad, uint32_t e, int G, const float* sv,
+                                                    const int32_t* sid, const uint64_t* mkey, const int32_t* rowoff,
+                                                    const int32_t* sbase, int k, int L) {
+    // a workgroup in which a wait gave up fails the step
+    const int any_bad = __syncthreads_or(bad);
+    if (threadIdx.x == 0) store_coherent(A.tpart + blockIdx.x, tagged(e, any_bad ? 1u : 0u));
+    if (blockIdx.x == G - 1) chain_outputs<NT>(A, sv, sid, mkey, rowoff, k, L);
+    if (blockIdx.x != 0) return;
+    if (L <= NT * 16) chain_logits_select<NT, 16>(A, e, G, rowoff, sbase, k, L);
+    else if (L <= NT * 32) chain_logits_select<NT, 32>(A, e, G, rowoff, sbase, k, L);
+    else chain_logits_select<NT, kChainLogits / NT>(A, e, G, rowoff, sbase, k, L);
 }
 
 template <int NB, int R, bool TOPK>
@@ -783,6 +949,7 @@ __global__ __launch_bounds__(kChainThreads) void chain_step_kernel(ChainArgs A) 
     if constexpr (!kEarly) load_h();
     GreedyState st;
     uint64_t wk = 0;  // top-k_t: this lane's place of the wave's key list
+    const bool hand_logits = TOPK && L <= kChainLogits;  // (uniform over the grid)
     {
         const int64_t p0 = (int64_t)gw * L / nw, p1 = (int64_t)(gw + 1) * L / nw;
         // slot q's cluster position: the number of clusters whose slabs end at
@@ -830,7 +997,7 @@ __global__ __launch_bounds__(kChainThreads) void chain_step_kernel(ChainArgs A) 
             for (int r = 1; r < R; ++r)
                 if (lane == r) my_row = lrow[r];
             const bool own = lane < nrow;
-            const int32_t vid = own ? A.perm[my_row] : 0;
+            const int32_t vid = own && !hand_logits ? A.perm[my_row] : 0;
             // row by row, so each row's dot starts as soon as its loads land
             float acc[R];
 #pragma unroll
@@ -847,9 +1014,10 @@ __global__ __launch_bounds__(kChainThreads) void chain_step_kernel(ChainArgs A) 
             }
             if (own) {
                 if (A.out_logits) A.out_logits[p + lane] = mine;
-                st.add(mine, vid, A.inv_t);
+                if (hand_logits) store_coherent(A.tpart + kChainStatus + p + lane, tagged(e, __float_as_uint(mine)));
+                else st.add(mine, vid, A.inv_t);
             }
-            if constexpr (TOPK) {
+            if (TOPK && !hand_logits) {
                 // the group's keys into the wave's list, one row at a time
                 // (branch-free: an empty key 0 leaves the list as it is)
                 const uint64_t mykey = own ? sel_key(mine != mine ? -__builtin_inff() : mine, (uint32_t)vid) : 0;
@@ -859,7 +1027,8 @@ __global__ __launch_bounds__(kChainThreads) void chain_step_kernel(ChainArgs A) 
         }
     }
     if constexpr (TOPK) {
-        chain_topk_finish<kChainThreads>(A, st, wk, bad, e, G, sv, sid, cand, rowoff, k, L);
+        if (hand_logits) chain_logits_finish<kChainThreads>(A, bad, e, G, sv, sid, cand, rowoff, sbase, k, L);
+        else chain_topk_finish<kChainThreads>(A, st, wk, bad, e, G, sv, sid, cand, rowoff, k, L);
         return;
     }
 

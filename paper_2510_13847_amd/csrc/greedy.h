@@ -171,7 +171,7 @@ __device__ __forceinline__ void block_softmax_pair(float m, float s, float inv_t
 // block-wide maxima.  out[0..k_t) gets the keys in descending order, 0 where
 // fewer exist; ends with a barrier.
 template <int L, int NT>
-__device__ void block_topk_lists(const uint64_t (&list)[L], int k_t, uint64_t* heads /* LDS [NT] */,
+__device__ __forceinline__ void block_topk_lists(const uint64_t (&list)[L], int k_t, uint64_t* heads /* LDS [NT] */,
                                  uint64_t* cand /* LDS [L * L] */, uint64_t* out /* LDS [k_t] */) {
     __shared__ uint64_t sh_T;
     __shared__ int sh_n;

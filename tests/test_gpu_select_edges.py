@@ -61,3 +61,40 @@ def test_top_kt(layout, kind, k_t):
             fin = np.isfinite(ref)
             # fp32: the exponentials' sum over at most 16385 terms in blocks of 16, and one logarithm
             assert np.abs(lp[b, :len(order)][fin] - ref[fin]).max() <= 1e-5 * max(1.0, np.abs(ref[fin]).max())
+
+
+# one context, one launch: shortlists to both sides of 4096, 8192 and 16384
+# slots (the blocks in which workgroup 0 reads the logits, and the key lists
+# beyond), with random rows and with equal ones
+@pytest.mark.parametrize("n", [1, 15, 4096, 4097, 8193, 16384, 16385])
+@pytest.mark.parametrize("equal", [False, True])
+@pytest.mark.parametrize("k_t", [2, 10, 16])
+def test_one_launch_top_kt(n, equal, k_t):
+    d, V, M = 64, 20000, 3
+    g = torch.Generator().manual_seed(n + k_t)
+    of = torch.full((V,), 2, dtype=torch.int32)
+    mine = torch.randperm(V, generator=g)[:n].sort().values
+    of[mine[: (n + 1) // 2]], of[mine[(n + 1) // 2:]] = 0, 1
+    W = (torch.randn((V, d), generator=g) / 8).to(torch.bfloat16)
+    if equal:
+        W[:] = W[0]
+    W1 = torch.zeros((M, d), dtype=torch.bfloat16)
+    W1[0, 0], W1[1, 0], W1[2, 0] = 2, 1, -1
+    h = torch.randn((1, d), generator=g).to(torch.bfloat16)
+    h[0, 0] = 1
+    L = D.build_layout(of.to(DEV), W.to(DEV), M)
+    D.set_option(D.OPT_FUSED_B1, 3)
+    try:
+        head = D.draft_head(D.Router(W1.to(DEV), act="none"), L, h.to(DEV), h.to(DEV), 2, mode=D.SEL_TOPK, k_t=k_t)
+        torch.cuda.synchronize()
+    finally:
+        D.set_option(D.OPT_FUSED_B1, 0)
+    assert head.clusters.cpu().tolist() == [[0, 1]]
+    z = head.logits[0, :n].cpu().numpy().astype(np.float64)
+    ids = mine.numpy()
+    assert np.abs(z - (W[mine].double() @ h[0].double()).numpy()).max() <= 1e-5
+    order = np.lexsort((ids, -z))[:k_t]
+    assert head.ids[0, :len(order)].cpu().tolist() == ids[order].tolist()
+    assert (head.ids[0, len(order):].cpu() == -1).all()
+    ref = z[order] - z.max() - np.log(np.exp(z - z.max()).sum())
+    assert np.abs(head.logprobs[0, :len(order)].cpu().numpy() - ref).max() <= 1e-5 * max(1.0, np.abs(ref).max())
