@@ -20,6 +20,11 @@ constexpr int kChunkRows = kMfmaRows;
 typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
 typedef float f32x4 __attribute__((ext_vector_type(4)));
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
+// Four words at any word address: one store instruction.  A lane's four rows
+// of an MFMA result written one by one scatter each instruction over 64
+// separate words.
+typedef float f32x4_w __attribute__((ext_vector_type(4), aligned(4)));
+typedef int i32x4_w __attribute__((ext_vector_type(4), aligned(4)));
 
 // A work chunk of the gathered head: up to kChunkRows consecutive layout rows
 // of one cluster and the list of contexts that selected that cluster.

@@ -347,12 +347,19 @@ __global__ __launch_bounds__(NW * kWave) void gather_ring_kernel(RowdotArgs a) {
                     __syncthreads();
                 }
                 if (store && col < ncols) {
+                    const int row0 = 4 * kq;
+                    if (row0 + 4 <= cu.nrows) {
+                        *reinterpret_cast<f32x4_w*>(a.out + obase + row0) = tile;
+                        if (a.vid_out != nullptr)
+                            *reinterpret_cast<i32x4_w*>(a.vid_out + obase + row0) = i32x4_w{vid[0], vid[1], vid[2], vid[3]};
+                    } else {
 #pragma unroll
-                    for (int r = 0; r < 4; ++r) {
-                        const int row = 4 * kq + r;
-                        if (row < cu.nrows) {
-                            a.out[obase + row] = tile[r];
-                            if (a.vid_out != nullptr) a.vid_out[obase + row] = vid[r];
+                        for (int r = 0; r < 4; ++r) {
+                            const int row = row0 + r;
+                            if (row < cu.nrows) {
+                                a.out[obase + row] = tile[r];
+                                if (a.vid_out != nullptr) a.vid_out[obase + row] = vid[r];
+                            }
                         }
                     }
                 }
@@ -678,10 +685,13 @@ __global__ __launch_bounds__(NW * kWave) void union_gemm_kernel(RowdotArgs a) {
                 for (int j = 0; j < NT; ++j) {
                     const int b = cu.g * NCOL + 16 * j + col;
                     if (b < B) {
+                        float* o = a.out + (int64_t)b * a.ld + base + 4 * kq;
+                        if (4 * kq + 4 <= cu.nrows[t]) {
+                            *reinterpret_cast<f32x4_w*>(o) = acc[t][j];
+                        } else {
 #pragma unroll
-                        for (int r = 0; r < 4; ++r) {
-                            const int row = 4 * kq + r;
-                            if (row < cu.nrows[t]) a.out[(int64_t)b * a.ld + base + row] = acc[t][j][r];
+                            for (int r = 0; r < 4; ++r)
+                                if (4 * kq + r < cu.nrows[t]) o[r] = acc[t][j][r];
                         }
                     }
                 }

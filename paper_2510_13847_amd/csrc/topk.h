@@ -51,16 +51,19 @@ __host__ __device__ inline size_t topk_lds_bytes(int M, int k) {
 }
 
 // The k best of the M scores sv[] (LDS) by (score desc, id asc), by one
-// workgroup of kNT threads.  On return (after a barrier) sel[0..k) holds the
+// workgroup of NT >= 256 threads.  On return (after a barrier) sel[0..k) holds the
 // k selection keys in no particular order, and the int32 arrays rk = (int32_t*)cand
 // and ik = rk + k hold, for each key, its rank and its position in ascending
 // id order.  `cand` is LDS scratch of M keys.
-__device__ void topk_core(const float* sv, int M, int k, uint64_t* sel, uint64_t* cand) {
+template <int NT>
+__device__ __forceinline__ void topk_core(const float* sv, int M, int k, uint64_t* sel, uint64_t* cand) {
     __shared__ int hist[256], hist2[256];
     __shared__ uint32_t sh_prefix;
     __shared__ int sh_krem, sh_nsel, sh_ncand;
-    hist[threadIdx.x] = 0;
-    hist2[threadIdx.x] = 0;
+    if (threadIdx.x < 256) {
+        hist[threadIdx.x] = 0;
+        hist2[threadIdx.x] = 0;
+    }
     if (threadIdx.x == 0) {
         sh_nsel = 0;
         sh_ncand = 0;
@@ -68,14 +71,14 @@ __device__ void topk_core(const float* sv, int M, int k, uint64_t* sel, uint64_t
     __syncthreads();
 
     // pass 1: top byte
-    for (int j = threadIdx.x; j < M; j += kNT) atomicAdd(&hist[ord_f32(sv[j]) >> 24], 1);
+    for (int j = threadIdx.x; j < M; j += NT) atomicAdd(&hist[ord_f32(sv[j]) >> 24], 1);
     __syncthreads();
     if (threadIdx.x < kWave) radix_digit(hist, k, 0u, 24, &sh_prefix, &sh_krem);
     __syncthreads();
     const uint32_t p1 = sh_prefix;
     const int krem1 = sh_krem;
     // pass 2: second byte inside the chosen top byte
-    for (int j = threadIdx.x; j < M; j += kNT) {
+    for (int j = threadIdx.x; j < M; j += NT) {
         const uint32_t o = ord_f32(sv[j]);
         if ((o & 0xff000000u) == p1) atomicAdd(&hist2[(o >> 16) & 255u], 1);
     }
@@ -86,7 +89,7 @@ __device__ void topk_core(const float* sv, int M, int k, uint64_t* sel, uint64_t
     const int need = sh_krem;             // places left for codes with prefix P
 
     // codes above P are in; codes with prefix P are ranked below
-    for (int j = threadIdx.x; j < M; j += kNT) {
+    for (int j = threadIdx.x; j < M; j += NT) {
         const uint32_t o = ord_f32(sv[j]);
         const uint64_t key = (static_cast<uint64_t>(o) << 32) | (0xffffffffu - (uint32_t)j);
         if ((o >> 16) > P) sel[atomicAdd(&sh_nsel, 1)] = key;
@@ -94,7 +97,7 @@ __device__ void topk_core(const float* sv, int M, int k, uint64_t* sel, uint64_t
     }
     __syncthreads();
     const int nsel0 = sh_nsel, ncand = sh_ncand;
-    for (int c = threadIdx.x; c < ncand; c += kNT) {
+    for (int c = threadIdx.x; c < ncand; c += NT) {
         const uint64_t key = cand[c];
         int rank = 0;
         for (int j = 0; j < ncand; ++j) rank += cand[j] > key;
@@ -107,15 +110,15 @@ __device__ void topk_core(const float* sv, int M, int k, uint64_t* sel, uint64_t
     // (the tie-candidate array is free again and holds the two counts)
     int32_t* rk = reinterpret_cast<int32_t*>(cand);  // [k]
     int32_t* ik = rk + k;                             // [k]
-    for (int i = threadIdx.x; i < k; i += kNT) {
+    for (int i = threadIdx.x; i < k; i += NT) {
         rk[i] = 0;
         ik[i] = 0;
     }
     __syncthreads();
     {
-        const int S = max(1, kNT / k);
+        const int S = max(1, NT / k);
         const int span = (k + S - 1) / S;
-        for (int wi = threadIdx.x; wi < k * S; wi += kNT) {
+        for (int wi = threadIdx.x; wi < k * S; wi += NT) {
             const int i = wi % k, sl = wi / k;
             const uint64_t key = sel[i];
             const uint32_t id = key_id(key);
@@ -133,9 +136,10 @@ __device__ void topk_core(const float* sv, int M, int k, uint64_t* sel, uint64_t
     __syncthreads();
 }
 
-// Row b of the selection, by one workgroup of kTopkThreads threads; `smem`
+// Row b of the selection, by one workgroup of NT threads; `smem`
 // holds topk_lds_bytes(M, k) bytes of LDS.
-__device__ void topk_row(const TopkArgs& A, int b, unsigned char* smem) {
+template <int NT>
+__device__ __forceinline__ void topk_row(const TopkArgs& A, int b, unsigned char* smem) {
     const int M = A.M, k = A.k;
     const float* __restrict__ scores = A.scores;
     int32_t* __restrict__ topk_ids = A.topk_ids;
@@ -151,12 +155,12 @@ __device__ void topk_row(const TopkArgs& A, int b, unsigned char* smem) {
     uint64_t* cand = sel + k;                                          // [M] tie candidates
     int32_t* sid = reinterpret_cast<int32_t*>(cand + M);               // [k] ids ascending
     int32_t* ssize = sid + k;                                          // [k]
-    __shared__ int tmp[kNT / kWave + 1];
+    __shared__ int tmp[NT / kWave + 1];
 
     // stage scores (and offsets) with kStagePer loads in flight per thread;
     // split-K partial sums are added here in slice order, then the bias
     const float* s = scores + (int64_t)b * M;
-    for (int j0 = 0; j0 < M; j0 += kNT * kStagePer) {
+    for (int j0 = 0; j0 < M; j0 += NT * kStagePer) {
         float x[kStagePer];
         if (A.part != nullptr) {
             // eight slices' loads are issued together, then added in order
@@ -169,7 +173,7 @@ __device__ void topk_row(const TopkArgs& A, int b, unsigned char* smem) {
                     const float* ps = A.part + ((int64_t)(sl0 + u) * gridDim.x + b) * M;
 #pragma unroll
                     for (int q = 0; q < kStagePer; ++q) {
-                        const int j = j0 + q * kNT + threadIdx.x;
+                        const int j = j0 + q * NT + threadIdx.x;
                         y[u][q] = (sl0 + u < A.slices && j < M) ? ps[j] : 0.0f;
                     }
                 }
@@ -181,41 +185,41 @@ __device__ void topk_row(const TopkArgs& A, int b, unsigned char* smem) {
             }
 #pragma unroll
             for (int q = 0; q < kStagePer; ++q) {
-                const int j = j0 + q * kNT + threadIdx.x;
+                const int j = j0 + q * NT + threadIdx.x;
                 if (j < M) x[q] = x[q] + (A.bias ? A.bias[j] : 0.0f);
             }
         } else {
 #pragma unroll
             for (int q = 0; q < kStagePer; ++q) {
-                const int j = j0 + q * kNT + threadIdx.x;
+                const int j = j0 + q * NT + threadIdx.x;
                 x[q] = j < M ? s[j] : 0.0f;
             }
         }
 #pragma unroll
         for (int q = 0; q < kStagePer; ++q) {
-            const int j = j0 + q * kNT + threadIdx.x;
+            const int j = j0 + q * NT + threadIdx.x;
             if (j < M) sv[j] = x[q];
         }
     }
     if (sel_sorted != nullptr) {
-        for (int j0 = 0; j0 <= M; j0 += kNT * kStagePer) {
+        for (int j0 = 0; j0 <= M; j0 += NT * kStagePer) {
             int x[kStagePer];
 #pragma unroll
             for (int q = 0; q < kStagePer; ++q) {
-                const int j = j0 + q * kNT + threadIdx.x;
+                const int j = j0 + q * NT + threadIdx.x;
                 x[q] = j <= M ? offsets[j] : 0;
             }
 #pragma unroll
             for (int q = 0; q < kStagePer; ++q) {
-                const int j = j0 + q * kNT + threadIdx.x;
+                const int j = j0 + q * NT + threadIdx.x;
                 if (j <= M) offs[j] = x[q];
             }
         }
     }
-    topk_core(sv, M, k, sel, cand);
+    topk_core<NT>(sv, M, k, sel, cand);
     const int32_t* rk = reinterpret_cast<const int32_t*>(cand);
     const int32_t* ik = rk + k;
-    for (int i = threadIdx.x; i < k; i += kNT) {
+    for (int i = threadIdx.x; i < k; i += NT) {
         const uint32_t id = key_id(sel[i]);
         const int rank = rk[i], idrank = ik[i];
         topk_ids[(int64_t)b * k + rank] = (int32_t)id;
@@ -229,7 +233,7 @@ __device__ void topk_row(const TopkArgs& A, int b, unsigned char* smem) {
     __syncthreads();
 
     // shortlist: exclusive prefix of the sizes in ascending id order
-    const int per = (k + kNT - 1) / kNT;
+    const int per = (k + NT - 1) / NT;
     const int i0 = min(k, (int)threadIdx.x * per);
     const int i1 = min(k, i0 + per);
     int local = 0, lchunks = 0;
@@ -238,8 +242,8 @@ __device__ void topk_row(const TopkArgs& A, int b, unsigned char* smem) {
         lchunks += (ssize[i] + kChunkRows - 1) / kChunkRows;
     }
     int len, n_chunks = 0;
-    int run = block_exclusive_scan<kNT>(local, tmp, &len);
-    int crun = plan.hdr ? block_exclusive_scan<kNT>(lchunks, tmp, &n_chunks) : 0;
+    int run = block_exclusive_scan<NT>(local, tmp, &len);
+    int crun = plan.hdr ? block_exclusive_scan<NT>(lchunks, tmp, &n_chunks) : 0;
     for (int i = i0; i < i1; ++i) {
         const int m = sid[i];
         sel_sorted[(int64_t)b * k + i] = m;
