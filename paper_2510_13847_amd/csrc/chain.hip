@@ -23,7 +23,7 @@
 //   5. each workgroup publishes its greedy partial; workgroup 0 polls them,
 //      merges them in workgroup order and writes the token, and the last
 //      workgroup writes the selection outputs.  For top-k_t (k_t <= 16)
-//      over up to 16384 slots the waves hand over the logits themselves and
+//      over up to 16384 slots (rows of up to 6144 columns) the waves hand over the logits themselves and
 //      workgroup 0 selects from them; beyond, a partial also carries the
 //      workgroup's k_t best keys, and workgroup 0 takes the k_t best of all.
 //
@@ -949,7 +949,10 @@ __global__ __launch_bounds__(kChainThreads) void chain_step_kernel(ChainArgs A) 
     if constexpr (!kEarly) load_h();
     GreedyState st;
     uint64_t wk = 0;  // top-k_t: this lane's place of the wave's key list
-    const bool hand_logits = TOPK && L <= kChainLogits;  // (uniform over the grid)
+    // (uniform over the grid.  The widest instance keeps the key lists: with
+    // this path it takes 256 registers and more, and a compute unit then holds
+    // one workgroup in place of the two that steps on two streams need.)
+    const bool hand_logits = TOPK && NB < 16 && L <= kChainLogits;
     {
         const int64_t p0 = (int64_t)gw * L / nw, p1 = (int64_t)(gw + 1) * L / nw;
         // slot q's cluster position: the number of clusters whose slabs end at
@@ -1027,8 +1030,12 @@ __global__ __launch_bounds__(kChainThreads) void chain_step_kernel(ChainArgs A) 
         }
     }
     if constexpr (TOPK) {
-        if (hand_logits) chain_logits_finish<kChainThreads>(A, bad, e, G, sv, sid, cand, rowoff, sbase, k, L);
-        else chain_topk_finish<kChainThreads>(A, st, wk, bad, e, G, sv, sid, cand, rowoff, k, L);
+        if constexpr (NB < 16)
+            if (hand_logits) {
+                chain_logits_finish<kChainThreads>(A, bad, e, G, sv, sid, cand, rowoff, sbase, k, L);
+                return;
+            }
+        chain_topk_finish<kChainThreads>(A, st, wk, bad, e, G, sv, sid, cand, rowoff, k, L);
         return;
     }
 

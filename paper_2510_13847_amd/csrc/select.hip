@@ -711,7 +711,9 @@ dyna_status launch_topk_clusters(const float* scores, int32_t B, int32_t M, int3
     // four to eight scores per thread: 4096 clusters (128 contexts) 18.9 us
     // with 256 threads, 13.2 with 1024; 2048 (16 contexts) 12.5 with 256,
     // 11.1 with 512; at 1024 clusters more threads lose to their barriers
-    if (M <= 1024) return launch(std::integral_constant<int, 256>{});
+    // (more waves also take a few more bytes of static LDS; near the 160 KiB
+    // limit, about 10000 clusters, 256 threads still fit where 1024 would not)
+    if (M <= 1024 || lds > 156 * 1024) return launch(std::integral_constant<int, 256>{});
     if (M <= 2048) return launch(std::integral_constant<int, 512>{});
     return launch(std::integral_constant<int, 1024>{});
 }
