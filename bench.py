@@ -468,7 +468,7 @@ def bench_kmeans(w, args, D, torch):
                    "rounds": R, "timing": "one dyna_kmeans call (row norms, initial centroids, rounds, final sync)"},
         "cluster_sizes": {"min": int(sizes.min()), "max": int(sizes.max()), "empty": int((sizes == 0).sum())},
         "roofline": {"kernel": "k-means assignment: every row against every centroid on the matrix cores, argmax epilogue",
-                     "kernel_symbol": "union_gemm_kernel", "bound": "mfma",
+                     "kernel_symbol": "nearest_centroid_kernel", "bound": "mfma",
                      "achieved": round(flops / k_s / 1e12, 2), "peak": 2500.0, "unit": "TFLOP/s",
                      "frac": round(flops / k_s / 1e12 / 2500.0, 4), "traffic": None,
                      "flops_per_launch": int(flops), "avg_launch_us": round(k_s * 1e6, 2), "launches": int(k_n),

@@ -78,7 +78,7 @@ template <int F>
 __global__ __launch_bounds__(kAsThreads, 1) void nearest_centroid_kernel(AssignArgs a) {
     constexpr int SIDE = 64 * F;
     constexpr int HALF = SIDE * kAsRowB;     // bytes of the rows (or centroids) of a stage
-        constexpr int NI = SIDE / 8 / kAsWaves;  // loads per wave, stage and operand (8 rows each)
+    constexpr int NI = SIDE / 8 / kAsWaves;  // loads per wave, stage and operand (8 rows each)
     static_assert(NI % 2 == 0, "the slot rule takes a load's parity");
     extern __shared__ __attribute__((aligned(16))) char smem[];
     const int lane = lane_id();
