@@ -766,12 +766,11 @@ dyna_status launch_union_nt(const RowdotArgs& a, int cfg, hipStream_t stream) {
             if constexpr (NT >= 8) return launch_union_cfg<8, 2, 64, NT>(a, stream);
             else if constexpr (NT == 4) return launch_union_cfg<8, 1, 64, NT, 3>(a, stream);
             else if constexpr (NT == 2) return launch_union_cfg<4, 1, 64, NT, 3>(a, stream);
-            // up to 16 contexts: two-wave workgroups of 64-column stages
-            // (many small workgroups per CU).  Measured at ten rows over a
-            // union of 31.6k slots: 52.2 us against 60.3 with 128-column
-            // stages and 54-81 us for deeper rings or more rows per wave;
-            // the 16-context dense head 186 us (128 columns: 188; four-wave
-            // workgroups: 233)
+            // up to 16 contexts (rows beyond the row-streaming kernel's 8192
+            // columns): two-wave workgroups of 64-column stages (many small
+            // workgroups per CU).  Measured at ten contexts over 31.6k rows:
+            // 52.2 us against 60.3 with 128-column stages and 54-81 us for
+            // deeper rings or more rows per wave
             else return launch_union_cfg<2, 1, 64, NT, 3>(a, stream);
     }
 }
@@ -798,11 +797,10 @@ dyna_status launch_gather_lds(const RowdotArgs& a, hipStream_t stream) {
         case 8: return launch_ring_cfg<4, 3, 256, 4>(a, stream);
         case 9: return launch_ring_cfg<8, 4, 128, 8>(a, stream);
         default:
-            // a short shortlist (at most a few thousand chunks, as in the
-            // union steps of a few rows): four waves split each chunk's k
-            // dimension.  Measured at ten rows: 19.0 -> 17.2 us over a union
-            // of 5.9k rows, 26.0 -> 23.4 us over 9.2k rows; the other split
-            // shapes gained less or lost.
+            // a short shortlist (at most a few thousand chunks): four waves
+            // split each chunk's k dimension.  Measured at ten contexts: 19.0
+            // -> 17.2 us over 5.9k rows, 26.0 -> 23.4 us over 9.2k rows; the
+            // other split shapes gained less or lost.
             if (a.max_chunks_bound <= kSplitChunks) return launch_ring_cfg<4, 4, 128, 4>(a, stream);
             return launch_ring_cfg<2, 4, 256>(a, stream);  // two workgroups of two waves per CU
     }
@@ -829,10 +827,9 @@ dyna_status launch_union_argmax(const RowdotArgs& a, int cfg, hipStream_t stream
         case 5: return launch_union_cfg<4, 4, 64, 8, 3, 1>(a, stream);
         case 6: return launch_union_cfg<8, 2, 64, 8, 0, 1>(a, stream);
         case 7: return launch_union_cfg<8, 4, 64, 8, 2, 1>(a, stream);
-        // measured best: eight waves of two row tiles (256 rows) against 256
-        // centroids, double-buffered (two 64 KB stages).  The rows are
-        // re-read from HBM once per group of centroids, so wider groups cut
-        // the HBM bytes: 128-centroid groups measured 1.15-1.34x slower.
+        // eight waves of two row tiles (256 rows) against 256 centroids,
+        // double-buffered (two 64 KB stages): the fastest of these shapes,
+        // 1292 us where the nearest-centroid kernel takes 835
         default: return launch_union_cfg<8, 2, 64, 16, 2, 1>(a, stream);
     }
 }
