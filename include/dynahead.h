@@ -115,8 +115,8 @@ size_t dyna_layout_workspace_bytes(int32_t V, int32_t M);
  *  cap_by_k_host   HOST output [M + 1] (cap_by_k[0] = 0)
  *  max_cluster_host HOST output, may be NULL
  * Synchronises `stream` before returning.  A cluster id outside [0, M)
- * gives DYNA_ERR_DEVICE_DATA (outputs are then unspecified).  Empty clusters
- * are allowed. */
+ * gives DYNA_ERR_DEVICE_DATA: no row is copied (W_perm keeps what it held) and
+ * the other outputs are unspecified.  Empty clusters are allowed. */
 dyna_status dyna_build_layout(const int32_t* cluster_of, int32_t V, int32_t M,
                               const void* W_lm, int32_t wdtype, int32_t d,
                               void* W_perm, int32_t* perm, int32_t* offsets,

@@ -125,12 +125,17 @@ __global__ __launch_bounds__(kScanThreads) void layout_scan_kernel(int32_t M, in
     if (threadIdx.x == 0) offsets[M] = carry;
 }
 
+// perm[row] = token.  Tokens with an id outside [0, M) have no row; the rows
+// past the last cluster, which they leave over, hold -1.
 __global__ void layout_scatter_kernel(const int32_t* __restrict__ cluster_of, int32_t V, int32_t M,
                                       const int32_t* __restrict__ rank,
                                       const int32_t* __restrict__ base,
+                                      const int32_t* __restrict__ offsets,
                                       int32_t* __restrict__ perm) {
+    const int32_t covered = offsets[M];
     for (int64_t v = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; v < V;
          v += (int64_t)gridDim.x * blockDim.x) {
+        if (v >= covered) perm[v] = -1;
         const int c = cluster_of[v];
         if (c < 0 || c >= M) continue;
         const int64_t chunk = v / kChunk;
@@ -139,19 +144,20 @@ __global__ void layout_scatter_kernel(const int32_t* __restrict__ cluster_of, in
 }
 
 // W_perm[j] = W[perm[j]]: one wave per row, 16-byte vectors, kCopyFlight of
-// them in flight per lane, streamed past the caches on both sides.  A bad
-// cluster id leaves places of perm unwritten: an entry outside [0, V) copies
-// nothing (the host reports the id afterwards).
+// them in flight per lane, streamed past the caches on both sides.  Where a
+// bad cluster id leaves rows over, nothing is copied (the host reports the id
+// afterwards): W_perm stays as it was.
 constexpr int kCopyFlight = 8;
 __global__ __launch_bounds__(256) void layout_copy_rows_kernel(const u32x4* __restrict__ W,
                                                                u32x4* __restrict__ Wp,
                                                                const int32_t* __restrict__ perm,
-                                                               int32_t V, int32_t vec_per_row) {
+                                                               const int32_t* __restrict__ covered, int32_t V,
+                                                               int32_t vec_per_row) {
     const int lane = lane_id();
+    if (*covered != V) return;
     const int64_t j = blockIdx.x * (int64_t)(blockDim.x / kWave) + threadIdx.x / kWave;
     if (j >= V) return;  // whole wave
     const int64_t src = perm[j];
-    if (src < 0 || src >= V) return;
     const u32x4* s = W + src * vec_per_row;
     u32x4* d = Wp + j * vec_per_row;
     for (int i0 = lane; i0 < vec_per_row; i0 += kCopyFlight * kWave) {
@@ -200,7 +206,7 @@ dyna_status launch_cluster_csr(const int32_t* cluster_of, int32_t V, int32_t M, 
     if (dyna_status s = check_launch("layout_count_kernel"); s != DYNA_OK) return s;
     layout_scan_kernel<<<1, kScanThreads, 0, stream>>>(M, nchunks, cnt, offsets);
     if (dyna_status s = check_launch("layout_scan_kernel"); s != DYNA_OK) return s;
-    layout_scatter_kernel<<<(V + 255) / 256, 256, 0, stream>>>(cluster_of, V, M, rank, cnt, perm);
+    layout_scatter_kernel<<<(V + 255) / 256, 256, 0, stream>>>(cluster_of, V, M, rank, cnt, offsets, perm);
     return check_launch("layout_scatter_kernel");
 }
 
@@ -213,7 +219,7 @@ dyna_status launch_build_layout(const int32_t* cluster_of, int32_t V, int32_t M,
     const int elt = wdtype == DYNA_BF16 ? 2 : 4;
     const int32_t vec_per_row = (int32_t)((int64_t)d * elt / 16);
     layout_copy_rows_kernel<<<(unsigned)(((int64_t)V + 3) / 4), 256, 0, stream>>>(
-        static_cast<const u32x4*>(W_lm), static_cast<u32x4*>(W_perm), perm, V, vec_per_row);
+        static_cast<const u32x4*>(W_lm), static_cast<u32x4*>(W_perm), perm, offsets + M, V, vec_per_row);
     if (dyna_status s = check_launch("layout_copy_rows_kernel"); s != DYNA_OK) return s;
     // the offsets come back behind the copy, so that the GPU never waits for the host
     if (hipMemcpyAsync(host_offsets_out, offsets, sizeof(int32_t) * (size_t)(M + 1), hipMemcpyDeviceToHost,

@@ -2,6 +2,8 @@
 counting sort behind the layout, the nearest-centroid product and the update."""
 from __future__ import annotations
 
+import ctypes
+
 import numpy as np
 import pytest
 
@@ -37,6 +39,30 @@ def test_layout_bad_id_is_reported(bad):
     with pytest.raises(D.DynaError) as e:
         D.build_layout(torch.from_numpy(of).to(DEV), torch.zeros((5000, 8), dtype=torch.bfloat16, device=DEV), 7)
     assert e.value.status == D.ERR_DEVICE_DATA
+
+
+@pytest.mark.parametrize("bad", [[0], [4095, 4096, 8999], list(range(9000))])
+def test_layout_refused_leaves_the_weights(bad):
+    """A partition with a bad id is refused before any row is copied: W_perm keeps
+    what it held, whatever perm held before; perm lists the good tokens, then -1."""
+    V, M, d = 9000, 7, 16
+    of = np.random.default_rng(5).integers(0, M, V).astype(np.int32)
+    of[bad] = M
+    ofd = torch.from_numpy(of).to(DEV)
+    W = torch.randn((V, d), device=DEV).to(torch.bfloat16)
+    W_perm = torch.full_like(W, 3.0)
+    perm = torch.arange(V, dtype=torch.int32, device=DEV)  # every entry a valid row
+    offsets = torch.empty(M + 1, dtype=torch.int32, device=DEV)
+    cap, n = np.zeros(M + 1, np.int32), D.layout_workspace_bytes(V, M)
+    ws = torch.zeros(n, dtype=torch.uint8, device=DEV)
+    status = D.lib().dyna_build_layout(ofd.data_ptr(), V, M, W.data_ptr(), D.BF16, d, W_perm.data_ptr(),
+                                       perm.data_ptr(), offsets.data_ptr(), cap.ctypes.data_as(ctypes.c_void_p), None,
+                                       ws.data_ptr(), n, torch.cuda.current_stream().cuda_stream)
+    assert status == D.ERR_DEVICE_DATA
+    assert bool((W_perm == 3.0).all())
+    good = np.flatnonzero(of < M)
+    good = good[np.argsort(of[good], kind="stable")]
+    assert perm.cpu().tolist() == good.tolist() + [-1] * (V - good.size)
 
 
 # both tile sides (128, and 256 from 256 tiles on), rows and centroids on
