@@ -5,6 +5,7 @@
 // consecutive rows turns the shortlist gather of the head into whole-slab
 // streams.  The layout is a stable counting sort of the tokens by cluster id
 // (ties keep ascending vocabulary id), followed by a row-permuting copy.
+#include <algorithm>
 #include <atomic>
 
 #include "dyna_device.h"
@@ -146,8 +147,11 @@ __global__ void layout_scatter_kernel(const int32_t* __restrict__ cluster_of, in
 // W_perm[j] = W[perm[j]]: one wave per row, 16-byte vectors, kCopyFlight of
 // them in flight per lane, streamed past the caches on both sides.  Where a
 // bad cluster id leaves rows over, nothing is copied (the host reports the id
-// afterwards): W_perm stays as it was.
+// afterwards): W_perm stays as it was.  One row per wave up to kCopyBlocks
+// workgroups (16.8 million rows); a launch holds less than 2^32 threads, so
+// longer tables go round.
 constexpr int kCopyFlight = 8;
+constexpr int64_t kCopyBlocks = 1 << 22;
 __global__ __launch_bounds__(256) void layout_copy_rows_kernel(const u32x4* __restrict__ W,
                                                                u32x4* __restrict__ Wp,
                                                                const int32_t* __restrict__ perm,
@@ -155,19 +159,20 @@ __global__ __launch_bounds__(256) void layout_copy_rows_kernel(const u32x4* __re
                                                                int32_t vec_per_row) {
     const int lane = lane_id();
     if (*covered != V) return;
-    const int64_t j = blockIdx.x * (int64_t)(blockDim.x / kWave) + threadIdx.x / kWave;
-    if (j >= V) return;  // whole wave
-    const int64_t src = perm[j];
-    const u32x4* s = W + src * vec_per_row;
-    u32x4* d = Wp + j * vec_per_row;
-    for (int i0 = lane; i0 < vec_per_row; i0 += kCopyFlight * kWave) {
-        u32x4 x[kCopyFlight];
+    const int64_t stride = (int64_t)gridDim.x * (blockDim.x / kWave);
+    for (int64_t j = blockIdx.x * (int64_t)(blockDim.x / kWave) + threadIdx.x / kWave; j < V; j += stride) {
+        const int64_t src = perm[j];
+        const u32x4* s = W + src * vec_per_row;
+        u32x4* d = Wp + j * vec_per_row;
+        for (int i0 = lane; i0 < vec_per_row; i0 += kCopyFlight * kWave) {
+            u32x4 x[kCopyFlight];
 #pragma unroll
-        for (int q = 0; q < kCopyFlight; ++q)
-            if (i0 + q * kWave < vec_per_row) x[q] = __builtin_nontemporal_load(s + i0 + q * kWave);
+            for (int q = 0; q < kCopyFlight; ++q)
+                if (i0 + q * kWave < vec_per_row) x[q] = __builtin_nontemporal_load(s + i0 + q * kWave);
 #pragma unroll
-        for (int q = 0; q < kCopyFlight; ++q)
-            if (i0 + q * kWave < vec_per_row) __builtin_nontemporal_store(x[q], d + i0 + q * kWave);
+            for (int q = 0; q < kCopyFlight; ++q)
+                if (i0 + q * kWave < vec_per_row) __builtin_nontemporal_store(x[q], d + i0 + q * kWave);
+        }
     }
 }
 
@@ -218,7 +223,8 @@ dyna_status launch_build_layout(const int32_t* cluster_of, int32_t V, int32_t M,
     if (dyna_status s = launch_cluster_csr(cluster_of, V, M, perm, offsets, ws, stream); s != DYNA_OK) return s;
     const int elt = wdtype == DYNA_BF16 ? 2 : 4;
     const int32_t vec_per_row = (int32_t)((int64_t)d * elt / 16);
-    layout_copy_rows_kernel<<<(unsigned)(((int64_t)V + 3) / 4), 256, 0, stream>>>(
+    const int64_t blocks = std::min<int64_t>(((int64_t)V + 3) / 4, kCopyBlocks);
+    layout_copy_rows_kernel<<<(unsigned)blocks, 256, 0, stream>>>(
         static_cast<const u32x4*>(W_lm), static_cast<u32x4*>(W_perm), perm, offsets + M, V, vec_per_row);
     if (dyna_status s = check_launch("layout_copy_rows_kernel"); s != DYNA_OK) return s;
     // the offsets come back behind the copy, so that the GPU never waits for the host

@@ -32,6 +32,21 @@ def test_layout(V, M, dtype, d):
     assert torch.equal(L.W_perm.cpu(), W[torch.from_numpy(perm)])
 
 
+def test_layout_of_more_rows_than_one_launch():
+    """2^26 rows and more need more waves than a launch can hold, one per row."""
+    V, M, d = (1 << 26) + 4999, 3, 8
+    g = torch.Generator(device=DEV).manual_seed(1)
+    of = torch.randint(0, M, (V,), generator=g, device=DEV, dtype=torch.int32)
+    W = torch.randint(-30000, 30000, (V, d), generator=g, device=DEV, dtype=torch.int16).view(torch.bfloat16)
+    L = D.build_layout(of, W, M)
+    assert L.offsets.cpu().tolist()[1:] == torch.bincount(of, minlength=M).cumsum(0).cpu().tolist()
+    perm = torch.argsort(of, stable=True)
+    assert torch.equal(L.perm.long(), perm)
+    W = W.view(torch.int16)
+    for r in range(0, V, 1 << 24):  # (torch's own indexing of all rows at once stops at 2^26)
+        assert torch.equal(L.W_perm[r:r + (1 << 24)].view(torch.int16), W[perm[r:r + (1 << 24)]])
+
+
 @pytest.mark.parametrize("bad", [-1, 7, 1 << 30])
 def test_layout_bad_id_is_reported(bad):
     of = np.zeros(5000, np.int32)
