@@ -49,13 +49,6 @@ constexpr int kAsSteps = kAsKB / 16;    // MFMA k steps of a stage
 constexpr int kAsRing = 3;              // stages of rows in LDS (and two of centroids)
 constexpr int kAsXcds = 8;              // workgroups go to the XCDs in turn
 
-// At most N of this wave's loads are outstanding, and its LDS reads are done.
-template <int N>
-__device__ __forceinline__ void wait_stage() {
-    static_assert(N < 16, "vmcnt low bits");
-    __builtin_amdgcn_s_waitcnt(N | 0x0070);
-}
-
 // 16 bytes per lane straight to LDS at dst + 16 * lane.
 __device__ __forceinline__ void load_lds16(__amdgpu_buffer_rsrc_t rsrc, char* dst, uint32_t voff, int soff) {
     __builtin_amdgcn_raw_ptr_buffer_load_lds(rsrc, (lds_ptr)dst, 16, (int)voff, soff, 0, 0);
@@ -251,8 +244,7 @@ __global__ __launch_bounds__(kAsThreads, 1) void nearest_centroid_kernel(AssignA
             // this stage has arrived (every wave's loads; only the next one's
             // rows may be missing), and every wave has read the last piece of
             // the stage before it
-            wait_stage<NI>();
-            __asm__ __volatile__("s_barrier" ::: "memory");
+            stage_barrier<NI>();
             if (kb > 0) {
                 // the last k step of the stage before
                 step(1, 0, [&](int m) {

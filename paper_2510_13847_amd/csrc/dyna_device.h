@@ -105,6 +105,33 @@ __device__ __forceinline__ float key_val(uint64_t key) {
     return ord_to_f32(static_cast<uint32_t>(key >> 32));
 }
 
+// ---------------------------------------------------------------- order
+// LDS accesses of this wave are complete and every wave of the workgroup has
+// arrived; loads from memory stay in flight.  The wait that counts is in one
+// statement with the barrier, so nothing can be moved between the two; the
+// builtin in front only tells the compiler what has been waited for.
+__device__ __forceinline__ void lds_barrier() {
+    __builtin_amdgcn_s_waitcnt(0xC07F);  // lgkmcnt(0) only
+    __asm__ __volatile__("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
+}
+
+// The same, once at most N of this wave's loads are outstanding.
+template <int N>
+__device__ __forceinline__ void stage_barrier() {
+    static_assert(N >= 0 && N < 16, "vmcnt low bits");
+    __builtin_amdgcn_s_waitcnt(N | 0x0070);
+    __asm__ __volatile__("s_waitcnt vmcnt(%0) lgkmcnt(0)\n\ts_barrier" ::"n"(N) : "memory");
+}
+
+// Between LDS accesses of a wave's lanes and accesses of its other lanes to
+// the same words.  A wave's LDS accesses complete in order; this keeps the
+// compiler from changing the order (no instruction).
+__device__ __forceinline__ void wave_lds_order() {
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront", "local");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront", "local");
+}
+
 // ---------------------------------------------------------------- wave ops
 // Cross-lane steps use DPP row shifts and row broadcasts (ALU latency)
 // instead of LDS permutes.  Source lanes outside a row read the identity.

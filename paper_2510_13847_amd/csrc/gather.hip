@@ -457,12 +457,6 @@ __device__ __forceinline__ void union_advance(UnionCursor<T>& u, int nkb, int ng
     union_set_tile<NW, T>(u, u.tile + gridDim.x, wv, plan, n_chunks);
 }
 
-// LDS reads of the previous stage are complete and every wave has arrived.
-__device__ __forceinline__ void stage_barrier() {
-    __builtin_amdgcn_s_waitcnt(0xC07F);  // lgkmcnt(0) only
-    __asm__ __volatile__("s_barrier" ::: "memory");
-}
-
 constexpr int kUnionLds = 160 * 1024;
 
 // SREQ: ring depth, or 0 for the deepest ring (at most 8) that fits in LDS
@@ -609,7 +603,7 @@ __global__ __launch_bounds__(NW * kWave) void union_gemm_kernel(RowdotArgs a) {
         // this wave's loads of stage q are done once at most the later stages remain
         if (issued - q - 1 == S - 2) wait_vmem<(S - 2) * NI>();
         else wait_vmem<0>();
-        stage_barrier();
+        lds_barrier();
         if (issued < Q) {
             issue((int)(issued % S));
             ++issued;

@@ -163,9 +163,7 @@ __global__ __launch_bounds__(kKmThreads, (J <= 2 ? 4 : 2)) void centroid_update_
             n = wave_sum(n);
             if (lane_id() == 0) red[at][threadIdx.x / kWave][q] = n;
         }
-        // LDS only: the next batch's loads stay in flight
-        __builtin_amdgcn_s_waitcnt(0xC07F);
-        __asm__ __volatile__("s_barrier" ::: "memory");
+        lds_barrier();  // the next batch's loads stay in flight
 #pragma unroll
         for (int q = 0; q < kKmUnroll; ++q) {
             float n = 0.0f;

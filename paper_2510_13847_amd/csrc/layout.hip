@@ -62,7 +62,7 @@ __global__ __launch_bounds__(kCountThreads) void layout_count_kernel(const int32
             // the group's last lane counts the group
             if ((same >> lane) == 1) own[c] = (uint16_t)(before + __popcll(same));
         }
-        __builtin_amdgcn_wave_barrier();
+        wave_lds_order();
     }
     __syncthreads();
     for (int m = threadIdx.x; m < M; m += blockDim.x) {

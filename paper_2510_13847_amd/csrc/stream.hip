@@ -49,13 +49,6 @@ constexpr int kStreamWaves = 8;
 constexpr int kStreamThreads = kStreamWaves * kWave;
 constexpr int kStreamXcds = 8;  // workgroups go to the XCDs in turn
 
-// LDS accesses of this wave are complete and every wave has arrived; loads
-// from memory stay in flight.
-__device__ __forceinline__ void lds_barrier() {
-    __builtin_amdgcn_s_waitcnt(0xC07F);  // lgkmcnt(0) only
-    __asm__ __volatile__("s_barrier" ::: "memory");
-}
-
 // NKS: 32-wide k steps of a stage per wave; SS: stages per tile (2 when a
 // wave's columns do not fit one stage); NG: groups of 16 contexts per
 // workgroup.  PIECES lanes cover one row's stage.
@@ -196,9 +189,10 @@ __global__ __launch_bounds__(kStreamThreads, (StreamShape<NKS, SS, NG>::EU)) voi
         StreamTile far{0, 0, 0};
 #pragma unroll
         for (int s = 0; s < SS; ++s) {
-            // each register is written to LDS (a wave's LDS accesses stay in
-            // order: the previous stage has been read) and loaded again at
-            // once, so the wave's loads stay in flight without a break
+            // each register is written to LDS (behind the previous stage's
+            // reads) and loaded again at once, so the wave's loads stay in
+            // flight without a break
+            wave_lds_order();
             const StreamTile& ld = s + 1 < SS ? cur : nxt;
             if (ld.nrows > 0) {
                 const __amdgpu_buffer_rsrc_t rsrc = tile_rsrc(ld);
@@ -215,6 +209,7 @@ __global__ __launch_bounds__(kStreamThreads, (StreamShape<NKS, SS, NG>::EU)) voi
                 if (vids && (int)threadIdx.x < nxt.nrows) vid_next = a.perm[nxt.r0 + threadIdx.x];
                 far = stream_tile<PLAN>(a, tile_at(n + 2), n_tiles);
             }
+            wave_lds_order();
 #pragma unroll
             for (int q = 0; q < NKS; ++q) {
                 const u32x4 w = *reinterpret_cast<const u32x4*>(rd + q * 64);
