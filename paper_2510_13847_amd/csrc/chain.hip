@@ -691,23 +691,39 @@ constexpr int kChainLogits = 16384;
 constexpr int kChainStatus = kChainMaxGrid;  // words ahead of the logits: one status per workgroup
 static_assert(kChainStatus + kChainLogits <= kPartWordsTopk * kChainMaxGrid, "the logits take the partials' place");
 
+constexpr int kChainKeys = 256;  // slots that may reach the bound (one per thread when ranked)
+
+// What workgroup 0 shares while it selects.
+struct ChainPick {
+    uint32_t group_max[4][16];
+    uint64_t group_key[4][16];
+    uint64_t sel[kChainKeys];
+    uint64_t top[kChainTopkMax], best[4];
+    float sum[4];
+    int n, bad;
+};
+
+// The rank of lane l's value among the 16 values of lanes 0..15 (lanes l and
+// l + 16 hold the same one); equal values rank by lane.
+template <typename F>
+__device__ __forceinline__ int rank16(F greater_or_earlier) {
+    int rank = 0;
+#pragma unroll
+    for (int j = 0; j < 16; ++j) rank += greater_or_earlier(j);
+    return rank;
+}
+
+// Polls the logits (P per thread) and the workgroups' statuses, and collects the slots that reach the
+// bound, as (value code, slot), in pk.sel; pk.n counts them all, also those
+// beyond kChainKeys.  Leaves the waves' softmax sums in pk.sum and returns
+// the largest value code; `bound` is the bound's code.
 template <int NT, int P>
-__device__ __forceinline__ void chain_logits_select(const ChainArgs& A, uint32_t e, int G, const int32_t* rowoff,
-                                                    const int32_t* sbase, int k, int L) {
+__device__ __forceinline__ uint32_t chain_logits_bound(const ChainArgs& A, uint32_t e, int G, int L, ChainPick& pk,
+                                                       bool& fail, uint32_t& bound) {
     constexpr int NW = NT / kWave;
-    constexpr int kKeys = 256;
-    static_assert(NT == kKeys, "one candidate per thread");
-    __shared__ uint32_t group_max[NW][16];
-    __shared__ uint64_t sel[kKeys];
-    __shared__ uint64_t s_top[kChainTopkMax], s_best[NW];
-    __shared__ float s_sum[NW];
-    __shared__ int s_n, s_bad;
+    static_assert(NW == 4 && NT == kChainKeys, "ChainPick's sizes");
     const int t = threadIdx.x, lane = lane_id(), w = t / kWave;
-    const int kt = A.k_t;
-    if (t == 0) s_n = s_bad = 0;
-    if (t < kt) s_top[t] = 0;
     uint32_t raw[P];
-    bool fail = false;
     constexpr int kFlight = 16;  // words of a thread polled together (32 gain nothing, and cost the second
                                  // workgroup per compute unit its registers)
 #pragma unroll
@@ -722,7 +738,7 @@ __device__ __forceinline__ void chain_logits_select(const ChainArgs& A, uint32_t
         fail |= poll_own<NT, 1>(A, A.tpart + g0, G - g0, e, st);
         fail |= g0 + t < G && st[0] != 0;
     }
-    const uint32_t err_word = load_coherent(A.err);
+    fail |= load_coherent(A.err) == e;
     // value codes (0: no slot)
     uint32_t m = 0;
 #pragma unroll
@@ -735,22 +751,18 @@ __device__ __forceinline__ void chain_logits_select(const ChainArgs& A, uint32_t
         const uint32_t y = (uint32_t)__builtin_amdgcn_ds_bpermute((lane ^ step) << 2, (int)m);
         m = y > m ? y : m;
     }
-    if (lane < 16) group_max[w][lane] = m;
+    if (lane < 16) pk.group_max[w][lane] = m;
     __syncthreads();
-    if (fail) s_bad = 1;
     uint32_t g = 0;
 #pragma unroll
-    for (int q = 0; q < NW; ++q) g = max(g, group_max[q][lane & 15]);
-    int rank = 0;
+    for (int q = 0; q < NW; ++q) g = max(g, pk.group_max[q][lane & 15]);
     uint32_t best = 0;
-#pragma unroll
-    for (int j = 0; j < 16; ++j) {
+    const int rank = rank16([&](int j) {
         const uint32_t y = (uint32_t)__builtin_amdgcn_readlane((int)g, j);
         best = max(best, y);
-        rank += y > g || (y == g && j < (lane & 15));
-    }
-    const uint32_t bound =
-        (uint32_t)__builtin_amdgcn_readlane((int)g, __builtin_ctzll(__ballot(rank == kt - 1 && lane < 16)));
+        return y > g || (y == g && j < (lane & 15));
+    });
+    bound = (uint32_t)__builtin_amdgcn_readlane((int)g, __builtin_ctzll(__ballot(rank == A.k_t - 1 && lane < 16)));
     // softmax mass, and the slots that reach the bound
     const float mx = best != 0 ? ord_to_f32(best) : -__builtin_inff();
     float sum = 0.0f;
@@ -759,68 +771,185 @@ __device__ __forceinline__ void chain_logits_select(const ChainArgs& A, uint32_t
         if (raw[q] == 0) continue;
         if (mx != -__builtin_inff()) sum += expf((ord_to_f32(raw[q]) - mx) * A.inv_t);
         if (raw[q] >= bound) {
-            const int i = atomicAdd(&s_n, 1);
-            if (i < kKeys) sel[i] = ((uint64_t)raw[q] << 32) | (uint32_t)(t + NT * q);
+            const int i = atomicAdd(&pk.n, 1);
+            if (i < kChainKeys) pk.sel[i] = ((uint64_t)raw[q] << 32) | (uint32_t)(t + NT * q);
         }
     }
     sum = wave_sum(sum);
-    if (lane == 0) s_sum[w] = sum;
-    __syncthreads();
-    // a slot's (value, vocabulary id) key
-    auto key_of = [&](uint32_t code, int slot) -> uint64_t {
-        int lo = 0, hi = k - 1;  // the first cluster whose slab ends past the slot
-        while (lo < hi) {
-            const int mid = (lo + hi) >> 1;
-            if (rowoff[mid + 1] > slot) hi = mid;
-            else lo = mid + 1;
+    if (lane == 0) pk.sum[w] = sum;
+    return best;
+}
+
+// More slots reach the bound's value than pk.sel holds: long runs of equal
+// logits (all of them, for a zero or NaN context).  Among equal values the
+// vocabulary id decides, so here every slot that reaches the value gets its
+// (value, id) key, and the bound is taken again over the keys: the k_t-th
+// largest of 16 group maxima.  Each thread keeps its four best keys for it;
+// one with more above the bound reads its slots again.  64 clusters, 8.2k
+// equal logits, k_t = 10: k_t rounds of a maximum over all the keys took 268
+// us a step.  Returns false, with the keys counted in pk.n, if even the keys
+// that reach this bound are more than kChainKeys.
+template <int NT, typename KeyOf>
+__device__ __forceinline__ bool chain_logits_equal(const ChainArgs& A, uint32_t bound, int L, ChainPick& pk,
+                                                   KeyOf keys_of) {
+    constexpr int NW = NT / kWave, U = 8, B = 4;
+    const int t = threadIdx.x, lane = lane_id(), w = t / kWave;
+    auto each = [&](auto f) __attribute__((always_inline)) {
+        for (int s0 = t; s0 < L; s0 += NT * U) {
+            uint64_t key[U];
+#pragma unroll
+            for (int q = 0; q < U; ++q) {
+                const int slot = min(s0 + NT * q, L - 1);
+                const uint32_t code =
+                    ord_f32(__uint_as_float((uint32_t)load_coherent(A.tpart + kChainStatus + slot)));
+                key[q] = ((uint64_t)code << 32) | (uint32_t)slot;
+            }
+            keys_of(key);
+#pragma unroll
+            for (int q = 0; q < U; ++q)
+                if (s0 + NT * q < L && (uint32_t)(key[q] >> 32) >= bound) f(key[q]);
         }
-        const uint32_t vid = (uint32_t)A.perm[(int64_t)sbase[lo] + (slot - rowoff[lo])];
-        return ((uint64_t)code << 32) | (0xffffffffu - vid);
     };
-    const int n = s_n;
-    if (n <= kKeys) {  // uniform
-        const uint64_t mine = t < n ? key_of((uint32_t)(sel[t] >> 32), (int)(uint32_t)sel[t]) : 0;
+    uint64_t mine[B] = {0, 0, 0, 0};
+    each([&](uint64_t key) {
+#pragma unroll
+        for (int r = 0; r < B; ++r) {
+            const uint64_t lower = key < mine[r] ? key : mine[r];
+            mine[r] = key < mine[r] ? mine[r] : key;
+            key = lower;
+        }
+    });
+    uint64_t m = mine[0];
+#pragma unroll
+    for (int step = 16; step <= 32; step <<= 1) {
+        const int src = (lane ^ step) << 2;
+        const uint64_t y = ((uint64_t)(uint32_t)__builtin_amdgcn_ds_bpermute(src, (int)(uint32_t)(m >> 32)) << 32) |
+                           (uint32_t)__builtin_amdgcn_ds_bpermute(src, (int)(uint32_t)m);
+        m = y > m ? y : m;
+    }
+    if (lane < 16) pk.group_key[w][lane] = m;
+    if (t == 0) pk.n = 0;
+    __syncthreads();
+    uint64_t g = 0;
+#pragma unroll
+    for (int q = 0; q < NW; ++q) {
+        const uint64_t y = pk.group_key[q][lane & 15];
+        g = y > g ? y : g;
+    }
+    const int rank = rank16([&](int j) {
+        const uint64_t y = readlane_u64(g, j);
+        return y > g || (y == g && j < (lane & 15));  // (empty groups are all 0)
+    });
+    const uint64_t least = readlane_u64(g, __builtin_ctzll(__ballot(rank == A.k_t - 1 && lane < 16)));
+    auto add = [&](uint64_t key) {
+        if (key == 0 || key < least) return;
+        const int i = atomicAdd(&pk.n, 1);
+        if (i < kChainKeys) pk.sel[i] = key;
+    };
+    if (mine[B - 1] != 0 && mine[B - 1] >= least) {
+        each(add);
+    } else {
+#pragma unroll
+        for (int r = 0; r < B - 1; ++r) add(mine[r]);
+    }
+    __syncthreads();
+    return pk.n <= kChainKeys;
+}
+
+// Workgroup 0: the k_t best of the L <= NT * P logits handed over.
+template <int NT, int P>
+__device__ __forceinline__ void chain_logits_select(const ChainArgs& A, uint32_t e, int G, const int32_t* rowoff,
+                                                    const int32_t* sbase, int k, int L, ChainPick& pk) {
+    constexpr int NW = NT / kWave;
+    const int t = threadIdx.x, lane = lane_id(), w = t / kWave;
+    const int kt = A.k_t;
+    if (t == 0) pk.n = pk.bad = 0;
+    if (t < kt) pk.top[t] = 0;
+    bool fail = false;
+    uint32_t bound;
+    const uint32_t best = chain_logits_bound<NT, P>(A, e, G, L, pk, fail, bound);
+    if (fail) pk.bad = 1;
+    __syncthreads();
+    // (value code, slot) pairs into (value, vocabulary id) keys
+    auto keys_of = [&](auto& key) __attribute__((always_inline)) {
+        constexpr int U = sizeof(key) / sizeof(uint64_t);
+        int lo[U], hi[U];
+#pragma unroll
+        for (int q = 0; q < U; ++q) {
+            lo[q] = 0;
+            hi[q] = k - 1;
+        }
+        // the first cluster whose slab ends past the slot
+        for (int span = k; span > 1; span = (span + 1) >> 1) {
+#pragma unroll
+            for (int q = 0; q < U; ++q) {
+                const int mid = (lo[q] + hi[q]) >> 1;
+                const bool left = rowoff[mid + 1] > (int)(uint32_t)key[q];
+                hi[q] = left ? mid : hi[q];
+                lo[q] = left ? lo[q] : min(mid + 1, hi[q]);
+            }
+        }
+#pragma unroll
+        for (int q = 0; q < U; ++q) {
+            const uint32_t vid = (uint32_t)A.perm[(int64_t)sbase[lo[q]] + ((int)(uint32_t)key[q] - rowoff[lo[q]])];
+            key[q] = (key[q] & 0xffffffff00000000ull) | (0xffffffffu - vid);
+        }
+    };
+    bool ranked = false;
+    if (pk.n <= kChainKeys) {  // uniform
+        uint64_t key[1] = {t < pk.n ? pk.sel[t] : 0};
+        if (key[0] != 0) keys_of(key);
         __syncthreads();
-        sel[t] = mine;
+        pk.sel[t] = key[0];
         __syncthreads();
-        if (mine != 0) {
+        ranked = true;
+    } else {
+        ranked = chain_logits_equal<NT>(A, bound, L, pk, keys_of);
+    }
+    if (ranked) {  // uniform
+        const int n = pk.n;
+        if (t < n) {
+            const uint64_t mine = pk.sel[t];
             int r = 0;
-            for (int j = 0; j < n; ++j) r += sel[j] > mine;
-            if (r < kt) s_top[r] = mine;
+            for (int j = 0; j < n; ++j) r += pk.sel[j] > mine;
+            if (r < kt) pk.top[r] = mine;
         }
     } else {
-        // long runs of equal logits: k_t rounds of a maximum below the last
+        // hundreds of large keys in fewer than k_t of the groups: k_t rounds
+        // of a maximum below the last
         uint64_t last = ~0ull;
         for (int r = 0; r < kt; ++r) {
             uint64_t b = 0;
-            for (int slot = t; slot < L; slot += NT) {  // (read again: the registers are not indexable)
-                const uint32_t code =
-                    ord_f32(__uint_as_float((uint32_t)load_coherent(A.tpart + kChainStatus + slot)));
-                if (code < bound) continue;
-                const uint64_t key = key_of(code, slot);
-                if (key < last && key > b) b = key;
+            for (int slot = t; slot < L; slot += NT) {
+                uint64_t key[1] = {
+                    ((uint64_t)ord_f32(__uint_as_float((uint32_t)load_coherent(A.tpart + kChainStatus + slot))) << 32) |
+                    (uint32_t)slot};
+                if ((uint32_t)(key[0] >> 32) < bound) continue;
+                keys_of(key);
+                if (key[0] < last && key[0] > b) b = key[0];
             }
             b = wave_max_u64(b);
-            if (lane == 0) s_best[w] = b;
+            if (lane == 0) pk.best[w] = b;
             __syncthreads();
-            b = s_best[0];
+            b = pk.best[0];
 #pragma unroll
-            for (int q = 1; q < NW; ++q) b = s_best[q] > b ? s_best[q] : b;
-            if (t == 0) s_top[r] = b;
+            for (int q = 1; q < NW; ++q) b = pk.best[q] > b ? pk.best[q] : b;
+            if (t == 0) pk.top[r] = b;
             last = b;
             __syncthreads();
         }
     }
     float total = 0.0f;
 #pragma unroll
-    for (int q = 0; q < NW; ++q) total += s_sum[q];
+    for (int q = 0; q < NW; ++q) total += pk.sum[q];
     __syncthreads();
-    const bool err = s_bad != 0 || err_word == e;
+    const bool err = pk.bad != 0;
     // every workgroup has read the epoch (its status carries it)
     if (t == 0) store_coherent(A.epoch, e);
+    const float mx = best != 0 ? ord_to_f32(best) : -__builtin_inff();
     const float lshift = (A.beta > 0.0f && (int64_t)A.V > L) ? log1pf(-A.beta) : 0.0f;
     if (t < kt) {
-        const uint64_t key = err ? 0 : s_top[t];
+        const uint64_t key = err ? 0 : pk.top[t];
         A.out_ids[t] = key != 0 ? (int32_t)key_id(key) : -1;
         if (A.out_logprobs)
             A.out_logprobs[t] = key != 0 ? (key_val(key) - mx) * A.inv_t - logf(total) + lshift : -__builtin_inff();
@@ -831,14 +960,15 @@ template <int NT>
 __device__ __forceinline__ void chain_logits_finish(const ChainArgs& A, bool bad, uint32_t e, int G, const float* sv,
                                                     const int32_t* sid, const uint64_t* mkey, const int32_t* rowoff,
                                                     const int32_t* sbase, int k, int L) {
+    __shared__ ChainPick pk;
     // a workgroup in which a wait gave up fails the step
     const int any_bad = __syncthreads_or(bad);
     if (threadIdx.x == 0) store_coherent(A.tpart + blockIdx.x, tagged(e, any_bad ? 1u : 0u));
     if (blockIdx.x == G - 1) chain_outputs<NT>(A, sv, sid, mkey, rowoff, k, L);
     if (blockIdx.x != 0) return;
-    if (L <= NT * 16) chain_logits_select<NT, 16>(A, e, G, rowoff, sbase, k, L);
-    else if (L <= NT * 32) chain_logits_select<NT, 32>(A, e, G, rowoff, sbase, k, L);
-    else chain_logits_select<NT, kChainLogits / NT>(A, e, G, rowoff, sbase, k, L);
+    if (L <= NT * 16) chain_logits_select<NT, 16>(A, e, G, rowoff, sbase, k, L, pk);
+    else if (L <= NT * 32) chain_logits_select<NT, 32>(A, e, G, rowoff, sbase, k, L, pk);
+    else chain_logits_select<NT, kChainLogits / NT>(A, e, G, rowoff, sbase, k, L, pk);
 }
 
 template <int NB, int R, bool TOPK>

@@ -98,3 +98,50 @@ def test_one_launch_top_kt(n, equal, k_t):
     assert (head.ids[0, len(order):].cpu() == -1).all()
     ref = z[order] - z.max() - np.log(np.exp(z - z.max()).sum())
     assert np.abs(head.logprobs[0, :len(order)].cpu().numpy() - ref).max() <= 1e-5 * max(1.0, np.abs(ref).max())
+
+
+# one launch, hundreds of slots at the bound of the selection: a run of equal
+# logits, the same value in every sixteenth slot (fewer groups than k_t hold
+# the largest), and contexts of zeros and NaN (every logit the same)
+@pytest.mark.parametrize("n", [300, 4097, 8193, 16384])
+@pytest.mark.parametrize("kind", ["run", "lanes", "lanes+1", "zero", "nan"])
+@pytest.mark.parametrize("k_t", [2, 10, 16])
+def test_one_launch_crowded_top_kt(n, kind, k_t):
+    d, V, M = 64, 20000, 3
+    g = torch.Generator().manual_seed(n + k_t)
+    of = torch.full((V,), 2, dtype=torch.int32)
+    mine = torch.randperm(V, generator=g)[:n].sort().values
+    mine = torch.cat([mine[::2], mine[1::2]])  # slot -> vocabulary id: two clusters, interleaved ids
+    of[mine[: (n + 1) // 2]], of[mine[(n + 1) // 2:]] = 0, 1
+    z = torch.randint(-99, 100, (n,), generator=g).float()
+    if kind == "run":
+        z[n // 4:n // 4 + 280] = 101
+    elif kind.startswith("lanes"):
+        z[5::16] = 101
+        if kind == "lanes+1":
+            z[[7, n - 1]] = 102
+    W = torch.zeros((V, d), dtype=torch.bfloat16)
+    W[mine, 1] = z.to(torch.bfloat16)
+    W1 = torch.zeros((M, d), dtype=torch.bfloat16)
+    W1[0, 0], W1[1, 0], W1[2, 0] = 2, 1, -1
+    x, h = torch.zeros((1, d), dtype=torch.bfloat16), torch.zeros((1, d), dtype=torch.bfloat16)
+    x[0, 0], h[0, 1] = 1, 1
+    if kind == "zero":
+        h[:] = 0
+        z[:] = 0
+    elif kind == "nan":
+        h[:] = float("nan")
+        z[:] = -float("inf")
+    L = D.build_layout(of.to(DEV), W.to(DEV), M)
+    D.set_option(D.OPT_FUSED_B1, 3)
+    try:
+        head = D.draft_head(D.Router(W1.to(DEV), act="none"), L, x.to(DEV), h.to(DEV), 2, mode=D.SEL_TOPK, k_t=k_t)
+        torch.cuda.synchronize()
+    finally:
+        D.set_option(D.OPT_FUSED_B1, 0)
+    order = np.lexsort((mine.numpy(), -z.numpy()))[:k_t]
+    assert head.ids[0].cpu().tolist() == mine.numpy()[order].tolist()
+    if kind != "nan":
+        zz = z.double().numpy()
+        ref = zz[order] - zz.max() - np.log(np.exp(zz - zz.max()).sum())
+        assert np.abs(head.logprobs[0].cpu().numpy() - ref).max() <= 1e-5 * max(1.0, np.abs(ref).max())
