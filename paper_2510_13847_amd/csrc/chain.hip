@@ -23,9 +23,10 @@
 //   5. each workgroup publishes its greedy partial; workgroup 0 polls them,
 //      merges them in workgroup order and writes the token, and the last
 //      workgroup writes the selection outputs.  For top-k_t (k_t <= 16)
-//      over up to 16384 slots (rows of up to 6144 columns) the waves hand over the logits themselves and
-//      workgroup 0 selects from them; beyond, a partial also carries the
-//      workgroup's k_t best keys, and workgroup 0 takes the k_t best of all.
+//      over a few thousand slots (rows of up to 6144 columns) the waves hand
+//      over the logits themselves and workgroup 0 selects from them; beyond, a
+//      partial also carries the workgroup's k_t best keys, and workgroup 0
+//      takes the k_t best of all.
 //
 // Hand-off protocol: every handed-off word is 64 bits, a 32-bit epoch tag
 // above the 32-bit value, written with one device-coherent store; readers
@@ -676,7 +677,7 @@ __device__ __forceinline__ void chain_topk_finish(const ChainArgs& A, const Gree
     }
 }
 
-// Stage 5 of the top-k_t step over up to kChainLogits shortlist slots: every
+// Stage 5 of the top-k_t step over up to chain_hands_logits slots: every
 // wave has handed over its logits themselves (one tagged word per slot, in
 // the partials' place), and workgroup 0 polls all of them at once and selects
 // from its registers.  One round trip of 8 bytes per slot takes the place of
@@ -685,9 +686,20 @@ __device__ __forceinline__ void chain_topk_finish(const ChainArgs& A, const Gree
 // selection is that of the row selection: the k_t-th largest of 16 group
 // maxima bounds the k_t-th value, and the few slots that reach it are ranked
 // by their (value, vocabulary id) keys.  Measured at 64 clusters, 8.0k slots
-// and k_t = 10, with the beam expansion: 37.1 -> 35.5 us (most of what is left is
-// workgroup 0 reading 64 KiB of coherent words).
-constexpr int kChainLogits = 16384;
+// and k_t = 10, with the beam expansion: 37.1 -> 34.9 us (most of what is left
+// is workgroup 0 reading 64 KiB of coherent words).
+constexpr int kChainLogits = 8192;
+// The slots up to which the hand-over is the faster form.  It costs workgroup
+// 0 a read of every slot, whatever k_t; the key lists cost every wave and
+// workgroup a list, the longer the larger k_t.  Steps of 1024 and 4096
+// columns, key lists against hand-over: 6.0k slots k_t = 2 21.7 and 20.4 us,
+// 27.6 and 27.2; 8.0k slots k_t = 2 22.7 and 23.6, 31.4 and 33.8, k_t = 4 23.7
+// and 24.3, k_t = 6 24.7 and 23.4, k_t = 10 28.3 and 27.0, 34.2 and 30.1; 10.0k
+// slots k_t = 10 30.1 and 29.3, 39.6 and 40.0; 14.0k slots k_t = 2 27.9 and
+// 33.1, k_t = 16 47.4 and 49.0.
+__device__ __forceinline__ bool chain_hands_logits(int L, int k_t) {
+    return L <= (k_t < 6 ? 6144 : kChainLogits);
+}
 constexpr int kChainStatus = kChainMaxGrid;  // words ahead of the logits: one status per workgroup
 static_assert(kChainStatus + kChainLogits <= kPartWordsTopk * kChainMaxGrid, "the logits take the partials' place");
 
@@ -967,7 +979,6 @@ __device__ __forceinline__ void chain_logits_finish(const ChainArgs& A, bool bad
     if (blockIdx.x == G - 1) chain_outputs<NT>(A, sv, sid, mkey, rowoff, k, L);
     if (blockIdx.x != 0) return;
     if (L <= NT * 16) chain_logits_select<NT, 16>(A, e, G, rowoff, sbase, k, L, pk);
-    else if (L <= NT * 32) chain_logits_select<NT, 32>(A, e, G, rowoff, sbase, k, L, pk);
     else chain_logits_select<NT, kChainLogits / NT>(A, e, G, rowoff, sbase, k, L, pk);
 }
 
@@ -1082,7 +1093,7 @@ __global__ __launch_bounds__(kChainThreads) void chain_step_kernel(ChainArgs A) 
     // (uniform over the grid.  The widest instance keeps the key lists: with
     // this path it takes 256 registers and more, and a compute unit then holds
     // one workgroup in place of the two that steps on two streams need.)
-    const bool hand_logits = TOPK && NB < 16 && L <= kChainLogits;
+    const bool hand_logits = TOPK && NB < 16 && chain_hands_logits(L, A.k_t);
     {
         const int64_t p0 = (int64_t)gw * L / nw, p1 = (int64_t)(gw + 1) * L / nw;
         // slot q's cluster position: the number of clusters whose slabs end at

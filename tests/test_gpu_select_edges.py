@@ -63,10 +63,11 @@ def test_top_kt(layout, kind, k_t):
             assert np.abs(lp[b, :len(order)][fin] - ref[fin]).max() <= 1e-5 * max(1.0, np.abs(ref[fin]).max())
 
 
-# one context, one launch: shortlists to both sides of 4096, 8192 and 16384
-# slots (the blocks in which workgroup 0 reads the logits, and the key lists
-# beyond), with random rows and with equal ones
-@pytest.mark.parametrize("n", [1, 15, 4096, 4097, 8193, 16384, 16385])
+# one context, one launch: shortlists to both sides of 4096 slots (the blocks
+# in which workgroup 0 reads the logits), of 6144 and of 8192 (the key lists
+# beyond, for small k_t and for all), and long ones, with random rows and with
+# equal ones
+@pytest.mark.parametrize("n", [1, 15, 4096, 4097, 6144, 6145, 8192, 8193, 16384, 16385])
 @pytest.mark.parametrize("equal", [False, True])
 @pytest.mark.parametrize("k_t", [2, 10, 16])
 def test_one_launch_top_kt(n, equal, k_t):
@@ -103,7 +104,7 @@ def test_one_launch_top_kt(n, equal, k_t):
 # one launch, hundreds of slots at the bound of the selection: a run of equal
 # logits, the same value in every sixteenth slot (fewer groups than k_t hold
 # the largest), and contexts of zeros and NaN (every logit the same)
-@pytest.mark.parametrize("n", [300, 4097, 8193, 16384])
+@pytest.mark.parametrize("n", [300, 4097, 6144, 8192, 16384])
 @pytest.mark.parametrize("kind", ["run", "lanes", "lanes+1", "zero", "nan"])
 @pytest.mark.parametrize("k_t", [2, 10, 16])
 def test_one_launch_crowded_top_kt(n, kind, k_t):
