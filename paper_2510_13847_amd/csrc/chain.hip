@@ -1094,7 +1094,10 @@ __global__ __launch_bounds__(kChainThreads) void chain_step_kernel(ChainArgs A) 
     // this path it takes 256 registers and more, and a compute unit then holds
     // one workgroup in place of the two that steps on two streams need.)
     const bool hand_logits = TOPK && NB < 16 && chain_hands_logits(L, A.k_t);
-    {
+    // (a loop for each form: the key lists' one ran 2% slower with the other's
+    // branches in it)
+    auto logits = [&](auto hand) __attribute__((always_inline)) {
+        constexpr bool HAND = decltype(hand)::value;
         const int64_t p0 = (int64_t)gw * L / nw, p1 = (int64_t)(gw + 1) * L / nw;
         // slot q's cluster position: the number of clusters whose slabs end at
         // or before q.  With k <= 64, lane i holds cluster i's end, start
@@ -1141,7 +1144,7 @@ __global__ __launch_bounds__(kChainThreads) void chain_step_kernel(ChainArgs A) 
             for (int r = 1; r < R; ++r)
                 if (lane == r) my_row = lrow[r];
             const bool own = lane < nrow;
-            const int32_t vid = own && !hand_logits ? A.perm[my_row] : 0;
+            const int32_t vid = own && !HAND ? A.perm[my_row] : 0;
             // row by row, so each row's dot starts as soon as its loads land
             float acc[R];
 #pragma unroll
@@ -1158,10 +1161,10 @@ __global__ __launch_bounds__(kChainThreads) void chain_step_kernel(ChainArgs A) 
             }
             if (own) {
                 if (A.out_logits) A.out_logits[p + lane] = mine;
-                if (hand_logits) store_coherent(A.tpart + kChainStatus + p + lane, tagged(e, __float_as_uint(mine)));
+                if constexpr (HAND) store_coherent(A.tpart + kChainStatus + p + lane, tagged(e, __float_as_uint(mine)));
                 else st.add(mine, vid, A.inv_t);
             }
-            if (TOPK && !hand_logits) {
+            if constexpr (TOPK && !HAND) {
                 // the group's keys into the wave's list, one row at a time
                 // (branch-free: an empty key 0 leaves the list as it is)
                 const uint64_t mykey = own ? sel_key(mine != mine ? -__builtin_inff() : mine, (uint32_t)vid) : 0;
@@ -1169,6 +1172,12 @@ __global__ __launch_bounds__(kChainThreads) void chain_step_kernel(ChainArgs A) 
                 for (int r = 0; r < R; ++r) wk = row_list_insert(wk, readlane_u64(mykey, r));
             }
         }
+    };
+    if constexpr (TOPK && NB < 16) {
+        if (hand_logits) logits(std::true_type{});
+        else logits(std::false_type{});
+    } else {
+        logits(std::false_type{});
     }
     if constexpr (TOPK) {
         if constexpr (NB < 16)
