@@ -668,9 +668,9 @@ __global__ __launch_bounds__(kNT) void select_final_kernel(SelectArgs a) {
     }
 }
 
-template <int KT>
+template <int KT, bool WIDE>
 __global__ __launch_bounds__(kRowThreads) void select_row_kernel(SelectArgs a) {
-    select_row<KT, kRowThreads>(a, blockIdx.x);
+    select_row<KT, kRowThreads, WIDE>(a, blockIdx.x);
 }
 
 }  // namespace
@@ -860,8 +860,9 @@ dyna_status launch_select(const float* logits, int64_t ld, const int32_t* row_le
     // shortlist-sized rows: one workgroup per row, one launch
     const bool split = split_long && max_len > kRowSplit;
     if (!split && select_row_fits(max_len, row_len == nullptr, k_t, perm == nullptr ? 0 : k)) {
-        if (k_t == 1) select_row_kernel<1><<<B, kRowThreads, 0, stream>>>(a);
-        else select_row_kernel<16><<<B, kRowThreads, 0, stream>>>(a);
+        if (k_t == 1) select_row_kernel<1, true><<<B, kRowThreads, 0, stream>>>(a);
+        else if (max_len <= 8 * kRowThreads) select_row_kernel<16, false><<<B, kRowThreads, 0, stream>>>(a);
+        else select_row_kernel<16, true><<<B, kRowThreads, 0, stream>>>(a);
         return check_launch("select_row_kernel");
     }
     if (a.seg == kSegShort) {

@@ -327,9 +327,12 @@ __device__ __forceinline__ bool block_bound_topk(const uint64_t (&kk)[P], int k_
 constexpr int kRowTable = 1024;  // clusters per row the LDS table holds
 constexpr int kRowThreads = 1024;  // threads per row: a few slots each
 
-template <int KT, int NT>
+// KT > 1 has two instances: rows of up to 8 slots per thread, and all rows
+// (WIDE).  What only long rows reach is marked unlikely: in line with the rest
+// it cost every row 0.45 us.
+template <int KT, int NT, bool WIDE>
 __device__ __forceinline__ void select_row(const SelectArgs& a, int b) {
-    __shared__ uint64_t cand[NT / kWave * KT];
+    __shared__ uint64_t cand[KT > 1 ? 1 : NT / kWave];
     __shared__ uint64_t top[KT];
     __shared__ float red[2 * (NT / kWave) + 1];
     __shared__ float incl_s[NT];
@@ -367,6 +370,15 @@ __device__ __forceinline__ void select_row(const SelectArgs& a, int b) {
     const bool sampling = a.uniforms != nullptr && a.out_sample != nullptr;
     __shared__ int rhist[KT > 1 ? 256 : 1];
     __shared__ uint64_t rsel[KT > 1 ? kBoundKeys : 1];
+    auto sum_of = [&](const auto& kk) __attribute__((always_inline)) {
+        const float mx = top[0] != 0 ? key_val(top[0]) : -__builtin_inff();
+        if (!sampling && mx != -__builtin_inff()) {
+#pragma unroll
+            for (uint64_t key : kk)
+                if (key != 0) tsum += expf((key_val(key) - mx) * a.inv_t);
+        }
+        summed = !sampling;
+    };
     auto in_registers = [&](auto per) __attribute__((always_inline)) {
         constexpr int P = decltype(per)::value;
         uint64_t kk[P];
@@ -376,27 +388,63 @@ __device__ __forceinline__ void select_row(const SelectArgs& a, int b) {
             kk[q] = j < len ? sel_key(canon(z[j]), vid_of(j)) : 0;
         }
         if (!block_bound_topk<NT, P>(kk, a.k_t, rsel, top)) {
+            // (16 keys and a radix selection's registers are too many)
             if constexpr (P <= 8) block_radix_topk<NT, P>(kk, a.k_t, len, rhist, rsel, top);
-            else return;  // (its registers do not hold 16 keys as well)
+            else return;
         }
         chosen = true;
-        const float mx = top[0] != 0 ? key_val(top[0]) : -__builtin_inff();
-        if (!sampling && mx != -__builtin_inff()) {
-#pragma unroll
-            for (int q = 0; q < P; ++q)
-                if (kk[q] != 0) tsum += expf((key_val(kk[q]) - mx) * a.inv_t);
-        }
-        summed = !sampling;
+        sum_of(kk);
     };
-    if constexpr (KT > 1) {
+    if constexpr (KT > 1 && !WIDE) {
+        if (len <= NT * 4) in_registers(std::integral_constant<int, 4>{});
+        else in_registers(std::integral_constant<int, 8>{});
+    } else if constexpr (KT > 1) {
         if (len <= NT * 4) in_registers(std::integral_constant<int, 4>{});
         else if (len <= NT * 8) in_registers(std::integral_constant<int, 8>{});
         else if (len <= NT * 16) in_registers(std::integral_constant<int, 16>{});
     }
-    if (!chosen) {  // uniform
-        uint64_t list[KT];
+    if constexpr (KT > 1 && WIDE) {
+        // Longer rows, and those of up to 16 slots per thread whose bound too
+        // many keys reach: block after block of 8 slots per thread, of which
+        // only the keys above the k_t-th best so far count (after the first
+        // blocks few, and most blocks end at one barrier).  The sorted lists
+        // that threads kept for these rows cost an insertion per slot: a step
+        // with 15 rows of 19.6k slots 117-125 us, with this 113.5; 22 rows of
+        // up to 128k 133-145 and 117.
+        if (__builtin_expect(!chosen, 0)) {
+            constexpr int P = 8;
+            __shared__ uint64_t more[KT];
+            if (threadIdx.x < KT) top[threadIdx.x] = 0;
+            __syncthreads();
+            for (int first = 0; first < len; first += NT * P) {
+                const uint64_t least = top[a.k_t - 1];
+                uint64_t kk[P];
+                bool any = false;
 #pragma unroll
-        for (int q = 0; q < KT; ++q) list[q] = 0;
+                for (int q = 0; q < P; ++q) {
+                    const int j = first + q * NT + (int)threadIdx.x;
+                    const uint64_t key = j < len ? sel_key(canon(z[j]), vid_of(j)) : 0;
+                    kk[q] = key > least ? key : 0;
+                    any |= kk[q] != 0;
+                }
+                if (!__syncthreads_or(any)) continue;  // (uniform)
+                if (!block_bound_topk<NT, P>(kk, a.k_t, rsel, more))
+                    block_radix_topk<NT, P>(kk, a.k_t, kBoundKeys + 1, rhist, rsel, more);
+                // the k_t best of both (a key's rank is the number of larger ones)
+                uint64_t key = 0;
+                int rank = 0;
+                if (threadIdx.x < 2 * KT) {
+                    const int i = threadIdx.x % KT;
+                    if (i < a.k_t) key = threadIdx.x < KT ? top[i] : more[i];
+                    for (int j = 0; j < a.k_t; ++j) rank += (top[j] > key) + (more[j] > key);
+                }
+                __syncthreads();
+                if (key != 0 && rank < a.k_t) top[rank] = key;
+                __syncthreads();
+            }
+        }
+    } else if constexpr (KT == 1) {
+        uint64_t list[1] = {0};
         // kLoadPer slots per thread per batch, their loads issued together
         constexpr int kLoadPer = 4;
         for (int j0 = 0; j0 < len; j0 += NT * kLoadPer) {
@@ -412,19 +460,10 @@ __device__ __forceinline__ void select_row(const SelectArgs& a, int b) {
             for (int q = 0; q < kLoadPer; ++q) {
                 if (j0 + q * NT + (int)threadIdx.x >= len) continue;
                 const uint64_t key = sel_key(canon(zq[q]), vq[q]);
-                if (key > list[KT - 1]) {
-                    list[KT - 1] = key;
-#pragma unroll
-                    for (int r = KT - 1; r > 0; --r)
-                        if (list[r] > list[r - 1]) {
-                            const uint64_t t = list[r];
-                            list[r] = list[r - 1];
-                            list[r - 1] = t;
-                        }
-                }
+                if (key > list[0]) list[0] = key;
             }
         }
-        block_topk_rounds<KT, NT, KT>(list, a.k_t, cand, top);
+        block_topk_rounds<1, NT, 1>(list, a.k_t, cand, top);
     }
     const float mx = top[0] != 0 ? key_val(top[0]) : -__builtin_inff();
 

@@ -146,3 +146,35 @@ def test_one_launch_crowded_top_kt(n, kind, k_t):
         zz = z.double().numpy()
         ref = zz[order] - zz.max() - np.log(np.exp(zz - zz.max()).sum())
         assert np.abs(head.logprobs[0].cpu().numpy() - ref).max() <= 1e-5 * max(1.0, np.abs(ref).max())
+
+
+# rows beyond 16 slots per thread go block after block: to both sides of two
+# and three blocks of 8192, with the best slots in one block, spread over all
+# of them, or of equal value, and rows that a long row stride makes the wide
+# kernel take
+@pytest.mark.parametrize("n", [1, 700, 5000, 16385, 24576, 24577, 60000])
+@pytest.mark.parametrize("kind", ["random", "rising", "falling", "equal", "runs", "lanes", "special"])
+@pytest.mark.parametrize("k_t", [2, 15, 16])
+def test_long_row_top_kt(n, kind, k_t):
+    rng = np.random.default_rng(n + k_t)
+    V, M = 70000, 2
+    of = np.ones(V, np.int32)
+    of[rng.permutation(V)[:n]] = 0
+    L = D.build_layout(torch.from_numpy(of).to(DEV), torch.zeros((V, 8), dtype=torch.bfloat16, device=DEV), M)
+    sel, off, length, ids = D.shortlist(L, torch.zeros((1, 1), dtype=torch.int32, device=DEV))
+    z = np.full((1, L.cap(1)), np.nan, np.float32)
+    z[0, :n] = np.sort(rng.standard_normal(n)) if kind in ("rising", "falling") else _logits(kind, n, rng)
+    if kind == "falling":
+        z[0, :n] = z[0, :n][::-1]
+    out = D.draft_select(L, torch.from_numpy(z).to(DEV), sel, off, length, mode=D.SEL_TOPK, k_t=k_t)
+    vids = ids.cpu().numpy()[0, :n]
+    zz = np.where(np.isnan(z[0, :n]), -np.inf, z[0, :n]).astype(np.float64)
+    order = np.lexsort((vids, -zz))[:k_t]
+    got = out["ids"].cpu().numpy()[0]
+    assert got[:len(order)].tolist() == vids[order].tolist() and (got[len(order):] == -1).all()
+    if np.isfinite(zz.max()):
+        ref = zz[order] - zz.max() - np.log(np.exp(zz - zz.max()).sum())
+        fin = np.isfinite(ref)
+        lp = out["logprobs"].cpu().numpy()[0, :len(order)]
+        # fp32: at most 64 terms per thread, a tree over 1024 threads, one logarithm
+        assert np.abs(lp[fin] - ref[fin]).max() <= 1e-5 * max(1.0, np.abs(ref[fin]).max())
