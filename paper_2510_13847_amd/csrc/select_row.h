@@ -304,15 +304,22 @@ __device__ __forceinline__ bool block_bound_topk(const uint64_t (&kk)[P], int k_
     __syncthreads();
     const int n = sh_count;
     if (n > kBoundKeys) return false;  // uniform
-    for (int i = threadIdx.x; i < max(n, k_t); i += NT) {
-        if (i >= n) {
+    // ranked by counting, S lanes sharing a key's count
+    constexpr int S = NT / kBoundKeys;
+    static_assert(S >= 1 && NT % kBoundKeys == 0, "every key has its lanes");
+    const int i = threadIdx.x / S;
+    const uint64_t key = i < n ? sel[i] : 0;
+    int r = 0;
+    if (i < n)
+        for (int j = threadIdx.x % S; j < n; j += S) r += sel[j] > key;
+#pragma unroll
+    for (int step = 1; step < S; step <<= 1) r += __shfl_xor(r, step);
+    if (threadIdx.x % S == 0) {
+        if (i < n) {
+            if (r < k_t) out[r] = key;
+        } else if (i < k_t) {
             out[i] = 0;  // a row of fewer than k_t keys
-            continue;
         }
-        const uint64_t key = sel[i];
-        int r = 0;
-        for (int j = 0; j < n; ++j) r += sel[j] > key;
-        if (r < k_t) out[r] = key;
     }
     __syncthreads();
     return true;
@@ -387,7 +394,12 @@ __device__ __forceinline__ void select_row(const SelectArgs& a, int b) {
             const int j = q * NT + threadIdx.x;
             kk[q] = j < len ? sel_key(canon(z[j]), vid_of(j)) : 0;
         }
-        if (!block_bound_topk<NT, P>(kk, a.k_t, rsel, top)) {
+        // k_t near 16 on rows of a few slots per thread: the bound is nearly the
+        // smallest group maximum, and the radix selection's passes are fewer
+        // than the keys that reach it (k_t = 16, two rows of 160 slots 23.0 ->
+        // 22.0 us a step, of 1.4k 25.2 -> 24.8; k_t = 14, 1.4k 24.8 -> 25.1)
+        const bool radix_first = !WIDE && P == 4 && a.k_t > 14;
+        if (radix_first || !block_bound_topk<NT, P>(kk, a.k_t, rsel, top)) {
             // (16 keys and a radix selection's registers are too many)
             if constexpr (P <= 8) block_radix_topk<NT, P>(kk, a.k_t, len, rhist, rsel, top);
             else return;
