@@ -680,11 +680,13 @@ __global__ __launch_bounds__(NW * kWave) void union_gemm_kernel(RowdotArgs a) {
                     const int b = cu.g * NCOL + 16 * j + col;
                     if (b < B) {
                         float* o = a.out + (int64_t)b * a.ld + base + 4 * kq;
-                        // one 16-byte store of four rows where it measured faster: up to
-                        // 64 contexts and output rows a multiple of 16 bytes apart
-                        // (64 contexts over 128256 x 4096 rows 262 -> 252 us); one
-                        // larger dense or union step took 663 us with it against 532
-                        if (NT <= 4 && a.ld % 4 == 0 && 4 * kq + 4 <= cu.nrows[t]) {
+                        // one 16-byte store of four rows, whatever its alignment (four
+                        // word stores scatter each instruction over 64 words):
+                        // dense 262144 x 4096 rows, 64 contexts 507 -> 486 us, 96: 587
+                        // -> 561; 200003 x 1536 rows, 128: 296 -> 260; a union over
+                        // 128256 x 4096 rows, 128 contexts 338 -> 318; no loss at
+                        // any of 90 shapes of 33-128 contexts
+                        if (4 * kq + 4 <= cu.nrows[t]) {
                             *reinterpret_cast<f32x4_w*>(o) = acc[t][j];
                         } else {
 #pragma unroll
