@@ -21,8 +21,6 @@ namespace dyna {
 namespace {
 
 constexpr int kKmThreads = 256;
-constexpr int kKmCols = 8 * kKmThreads;  // columns one pass of an update workgroup covers
-constexpr int kKmUnroll = 4;             // member rows whose loads are issued together
 
 // bf16 bits of x, rounded to nearest with ties to even (NaN stays a quiet NaN).
 __device__ __forceinline__ uint16_t to_bf16_rne(float x) {
@@ -93,22 +91,24 @@ __global__ void full_plan_kernel(int32_t V, int32_t B, Plan plan) {
 }
 
 // mu[m] = (sum of the unit rows of cluster m, in ascending row id) / its norm;
-// an empty cluster or a zero sum keeps mu[m].  One workgroup per cluster;
-// thread t owns columns 8t + 2048 j, j < J.  The rows stream in batches of
-// kKmUnroll, the next batch in flight while the current one's norms are
-// summed across the workgroup (a pass of its own for the norms read every
-// row once more: 152 us over 128256 x 4096 rows, and this kernel takes 190 us
-// with them against 207 without).  Bound by HBM (5.5 TB/s); the register
-// bound lets four workgroups share a compute unit, so that 1024 clusters run
-// at once (1116 us per round against 1133 with three).
-template <int J>
-__global__ __launch_bounds__(kKmThreads, (J <= 2 ? 4 : 2)) void centroid_update_kernel(const uint16_t* __restrict__ W,
-                                                                     const int32_t* __restrict__ perm,
-                                                                     const int32_t* __restrict__ offsets, int32_t d,
-                                                                     float* __restrict__ mu32,
-                                                                     uint16_t* __restrict__ mu16) {
-    constexpr int NW = kKmThreads / kWave;
-    __shared__ float red[2][NW][kKmUnroll];
+// an empty cluster or a zero sum keeps mu[m].  One workgroup of NT threads per
+// cluster; thread t owns columns 8 t + 8 NT j, j < J.  The rows stream in
+// batches of U, the next batch in flight while the current one's norms are
+// summed across the workgroup (a pass of its own for the norms read every row
+// once more: 152 us over 128256 x 4096 rows).  With many clusters it is bound
+// by HBM: 1024 clusters of 128256 x 4096 rows 190-197 us, 5.3-5.5 TB/s, with
+// EU waves per SIMD so that four workgroups share a compute unit and all
+// clusters run at once.  With few clusters a workgroup's time is its batches'
+// latency, so the batches are longer.
+template <int NT, int J, int U, int EU>
+__global__ __launch_bounds__(NT, EU) void centroid_update_kernel(const uint16_t* __restrict__ W,
+                                                                 const int32_t* __restrict__ perm,
+                                                                 const int32_t* __restrict__ offsets, int32_t d,
+                                                                 float* __restrict__ mu32,
+                                                                 uint16_t* __restrict__ mu16) {
+    constexpr int NW = NT / kWave;
+    constexpr int COLS = 8 * NT;  // columns one pass of the workgroup covers
+    __shared__ float red[2][NW][U];
     const int64_t m = blockIdx.x;
     const int32_t i0 = offsets[m], i1 = offsets[m + 1];
     if (i0 >= i1) return;  // empty: unchanged (whole workgroup)
@@ -117,19 +117,19 @@ __global__ __launch_bounds__(kKmThreads, (J <= 2 ? 4 : 2)) void centroid_update_
     for (int j = 0; j < J; ++j)
 #pragma unroll
         for (int e = 0; e < 8; ++e) s[j][e] = 0.0f;
-    u32x4 x[kKmUnroll][J], y[kKmUnroll][J];
-    int32_t v[kKmUnroll];
-    // rows i .. i + kKmUnroll - 1 (past the cluster: zeros, which add nothing)
+    u32x4 x[U][J], y[U][J];
+    int32_t v[U];
+    // rows i .. i + U - 1 (past the cluster: zeros, which add nothing)
     auto ids = [&](int32_t i) {
 #pragma unroll
-        for (int q = 0; q < kKmUnroll; ++q) v[q] = i + q < i1 ? perm[i + q] : -1;
+        for (int q = 0; q < U; ++q) v[q] = i + q < i1 ? perm[i + q] : -1;
     };
     auto load = [&]() {
 #pragma unroll
-        for (int q = 0; q < kKmUnroll; ++q)
+        for (int q = 0; q < U; ++q)
 #pragma unroll
             for (int j = 0; j < J; ++j) {
-                const int c0 = 8 * (int)threadIdx.x + kKmCols * j;
+                const int c0 = 8 * (int)threadIdx.x + COLS * j;
                 y[q][j] = u32x4{0u, 0u, 0u, 0u};
                 if (v[q] >= 0 && c0 < d)
                     y[q][j] = __builtin_nontemporal_load(reinterpret_cast<const u32x4*>(W + (int64_t)v[q] * d + c0));
@@ -137,20 +137,21 @@ __global__ __launch_bounds__(kKmThreads, (J <= 2 ? 4 : 2)) void centroid_update_
     };
     ids(i0);
     load();
-    ids(i0 + kKmUnroll);
+    ids(i0 + U);
     int at = 0;
-    for (int32_t i = i0; i < i1; i += kKmUnroll, at ^= 1) {
+    for (int32_t i = i0; i < i1; i += U, at ^= 1) {
 #pragma unroll
-        for (int q = 0; q < kKmUnroll; ++q)
+        for (int q = 0; q < U; ++q)
 #pragma unroll
             for (int j = 0; j < J; ++j) x[q][j] = y[q][j];
-        if (i + kKmUnroll < i1) {
+        if (i + U < i1) {
             load();
-            ids(i + 2 * kKmUnroll);
+            ids(i + 2 * U);
         }
         // the batch's squared norms (two places in turn: one barrier a batch)
+        float norm[U];
 #pragma unroll
-        for (int q = 0; q < kKmUnroll; ++q) {
+        for (int q = 0; q < U; ++q) {
             float n = 0.0f;
 #pragma unroll
             for (int j = 0; j < J; ++j)
@@ -160,15 +161,18 @@ __global__ __launch_bounds__(kKmThreads, (J <= 2 ? 4 : 2)) void centroid_update_
                     n = fmaf(lo, lo, n);
                     n = fmaf(hi, hi, n);
                 }
-            n = wave_sum(n);
-            if (lane_id() == 0) red[at][threadIdx.x / kWave][q] = n;
+            norm[q] = wave_sum(n);
+            if (NW > 1 && lane_id() == 0) red[at][threadIdx.x / kWave][q] = norm[q];
         }
-        lds_barrier();  // the next batch's loads stay in flight
+        if constexpr (NW > 1) lds_barrier();  // the next batch's loads stay in flight
 #pragma unroll
-        for (int q = 0; q < kKmUnroll; ++q) {
-            float n = 0.0f;
+        for (int q = 0; q < U; ++q) {
+            float n = norm[q];
+            if constexpr (NW > 1) {
+                n = 0.0f;
 #pragma unroll
-            for (int w = 0; w < NW; ++w) n += red[at][w][q];
+                for (int w = 0; w < NW; ++w) n += red[at][w][q];
+            }
             const float sc = n > 0.0f ? 1.0f / sqrtf(n) : 0.0f;  // an all-zero row adds nothing
 #pragma unroll
             for (int j = 0; j < J; ++j)
@@ -195,7 +199,7 @@ __global__ __launch_bounds__(kKmThreads, (J <= 2 ? 4 : 2)) void centroid_update_
     const float rn = 1.0f / sqrtf(tot);
 #pragma unroll
     for (int j = 0; j < J; ++j) {
-        const int c0 = 8 * (int)threadIdx.x + kKmCols * j;
+        const int c0 = 8 * (int)threadIdx.x + COLS * j;
         if (c0 < d) {
 #pragma unroll
             for (int e = 0; e < 8; ++e) {
@@ -274,16 +278,25 @@ dyna_status launch_assign(const uint16_t* W, int32_t V, int32_t d, const uint16_
 dyna_status launch_update(const uint16_t* W, int32_t V, int32_t d, const int32_t* assign, int32_t M,
                           const KmWs& w, float* mu32, hipStream_t stream) {
     if (dyna_status s = launch_cluster_csr(assign, V, M, w.perm, w.offsets, w.csr, stream); s != DYNA_OK) return s;
-    const int J = (d + kKmCols - 1) / kKmCols;
-#define DYNA_KM_UPD(NJ)                                                                                       \
-    if (J <= NJ) {                                                                                            \
-        centroid_update_kernel<NJ><<<M, kKmThreads, 0, stream>>>(W, w.perm, w.offsets, d, mu32, w.mu16); \
-        return check_launch("centroid_update_kernel");                                                        \
-    }
-    DYNA_KM_UPD(1)
-    DYNA_KM_UPD(2)
-    DYNA_KM_UPD(4)
-#undef DYNA_KM_UPD
+    auto launch = [&](int threads, auto kernel) -> dyna_status {
+        kernel<<<M, threads, 0, stream>>>(W, w.perm, w.offsets, d, mu32, w.mu16);
+        return check_launch("centroid_update_kernel");
+    };
+    // Long batches (16 rows; 8 beyond 2048 columns, whose registers hold no
+    // more) while the clusters are few, shorter ones and more workgroups per
+    // compute unit beyond; up to 512 columns a wave holds the whole row, and its
+    // sum needs no barrier.  Whole update of 128256 rows, with the norms'
+    // separate pass before, with batches of 4 everywhere, and now: 256 columns,
+    // 64 clusters 735, 1053 and 625 us, 1024: 231, 232, 142; 1024 columns, 64: 761,
+    // 970, 717, 768: 217, 161, 146; 4096 columns, 128: 692, 593, 576.
+    if (d <= 512) return launch(64, centroid_update_kernel<64, 1, 16, 2>);
+    if (d <= 2048)
+        return M <= 512 ? launch(256, centroid_update_kernel<256, 1, 16, 2>)
+                        : launch(256, centroid_update_kernel<256, 1, 8, 4>);
+    if (d <= 4096)
+        return M <= 256 ? launch(256, centroid_update_kernel<256, 2, 8, 2>)
+                        : launch(256, centroid_update_kernel<256, 2, 4, 4>);
+    if (d <= 8192) return launch(256, centroid_update_kernel<256, 4, 4, 2>);
     return set_error(DYNA_ERR_UNSUPPORTED, "k-means: d=%d > 8192", d);
 }
 

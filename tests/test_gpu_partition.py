@@ -128,3 +128,22 @@ def test_update(d):
         ref = torch.nn.functional.normalize(U[a == m].sum(dim=0), dim=0) if n else mu0[m].double()
         # a few fp32 roundings per element (the norm, the scale, up to nine sums)
         assert float((mu[m] - ref).abs().max()) <= 32 * 2.0 ** -24 * max(1.0, float(ref.abs().max()))
+
+
+@pytest.mark.parametrize("d", [512, 520, 2048, 2056, 4096, 4104])
+@pytest.mark.parametrize("copies", [1, 40, 70])
+def test_update_batches(d, copies):
+    """Clusters at the edges of every batch length (4, 8 and 16 rows), few and
+    many of them (each side of 256 and 512 clusters takes another batch)."""
+    g = torch.Generator().manual_seed(d + copies)
+    sizes = torch.tensor([1, 3, 4, 5, 8, 9, 16, 17] * copies)
+    M = len(sizes)
+    a = torch.arange(M, dtype=torch.int32).repeat_interleave(sizes)
+    a = a[torch.randperm(len(a), generator=g)]
+    W = torch.randn((len(a), d), generator=g).to(torch.bfloat16)
+    mu = D.kmeans_update(W.to(DEV), a.to(DEV), torch.zeros((M, d), device=DEV))
+    U = torch.nn.functional.normalize(W.to(DEV).double(), dim=1)
+    ref = torch.zeros((M, d), dtype=torch.float64, device=DEV).index_add_(0, a.to(DEV).long(), U)
+    ref = torch.nn.functional.normalize(ref, dim=1)
+    # a few fp32 roundings per element (the norm, the scale, up to 17 sums)
+    assert float((mu.double() - ref).abs().max()) <= 32 * 2.0 ** -24
