@@ -405,12 +405,9 @@ static int gathered_path(int32_t B) {
 }
 
 // Dense product of rows with every context: the row-streaming kernel where it
-// takes the shape, else (more contexts, or a fixed DYNA_OPT_UNION_CFG) the
-// union kernel.
+// takes the shape, else (more contexts, longer tables, or a fixed
+// DYNA_OPT_UNION_CFG) the union kernel, which walks a plan.
 static bool dense_rows_stream(const RowdotArgs& a) { return option_union_cfg() == 0 && row_stream_eligible(a); }
-static dyna_status launch_dense_rows(const RowdotArgs& a, hipStream_t s) {
-    return dense_rows_stream(a) ? launch_row_stream(a, s) : launch_union_gemm(a, s);
-}
 
 static dyna_status run_logits(const dyna_layout* L, const void* h, int32_t hdtype, int32_t B, int32_t k,
                               const int32_t* sel_sorted, const int32_t* sel_rowoff, float* logits,
@@ -818,7 +815,9 @@ dyna_status draft_head_core(const dyna_router* r, const dyna_layout* L, const vo
         want_sample ? out_sample_logprob : nullptr, c.select_ws, c.slot_vid);
     if (fused) return timed([&] { return launch_logits_greedy(a, sa, c.partials, c.counters, stream); }, stream);
     if (dense_union && !gather_lds_eligible(a)) return set_error(DYNA_ERR_UNSUPPORTED, "union: kernel arguments");
-    if (dense_union) TRY(timed([&] { return launch_dense_rows(a, stream); }, stream));
+    if (dense_union)
+        TRY(timed([&] { return dense_rows_stream(a) ? launch_row_stream(a, stream) : launch_union_gemm(a, stream); },
+                  stream));
     else TRY(timed_rowdot(a, union_mode ? option_logits_path() : gathered_path(B), stream));
     // union rows over a few thousand slots select faster in one launch (one
     // workgroup per row); long union rows split into segments.  Measured at
@@ -976,15 +975,16 @@ DYNA_API dyna_status dyna_dense_head(const void* W, int32_t wdtype, int32_t n_ro
     a.act = DYNA_ACT_NONE;
     a.n_rows = n_rows;
     if (option_logits_path() == 0 && B > 4 && wdtype == DYNA_BF16 && hdtype == DYNA_BF16) {
-        // several contexts: the rows streamed once through LDS by the union
-        // kernel, every context multiplied on the matrix cores
-        if (!dense_rows_stream(a)) {
-            // the union kernel walks a plan
+        // several contexts: the rows streamed once, every context multiplied on
+        // the matrix cores
+        if (dense_rows_stream(a)) {
+            TRY(timed([&] { return launch_row_stream(a, stream); }, stream));
+        } else {
             a.plan = plan;
             a.max_chunks_bound = plan.max_chunks;
             TRY(launch_full_plan(n_rows, B, plan, stream));
+            TRY(timed([&] { return launch_union_gemm(a, stream); }, stream));
         }
-        TRY(timed([&] { return launch_dense_rows(a, stream); }, stream));
     } else {
         TRY(timed_rowdot(a, option_logits_path(), stream));
     }

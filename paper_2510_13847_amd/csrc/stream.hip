@@ -306,17 +306,36 @@ dyna_status launch_stream_n(const RowdotArgs& a, hipStream_t stream) {
 
 // Up to 32 contexts (16 beyond 4096 columns) it was faster than the union
 // kernel at every size measured.  33-64 contexts share tiles between two
-// workgroups; there it is faster for short rows and where the union kernel's
-// first round of workgroups (512 of 128 rows) is not full: 40000 x 2560 rows
-// 54 us against 68, 16000 x 1536 16 against 28, 128256 x 2048 125 against
-// 138; but 128256 x 3072 181 against 166 and 128256 x 4096 236 against 229.
+// workgroups, and cost as much at 33 as at 64.  Against the union kernel they
+// win on tables too small to fill its 128-row tiles, and lose beyond; the
+// line lies by the row length.  Dense steps, union kernel against this, us:
+//   256 columns   40 contexts 16000 rows 21.5 and 19.9, 32000 23.9 and 25.7
+//   512           40          48000 33.4 and 31.9, 64000 36.3 and 37.7
+//   1024          40          64000 46.2 and 42.4, 128256 76.0 and 68.2,
+//                             262144 142.3 and 156.2
+//   1536          40          64000 57.7 and 55.2, 96000 78.0 and 84.4
+//   2048          48          64000 81.8 and 69.4, 200003 222.4 and 214.3
+//   4096          40          24000 75.5 and 67.5, 32000 77.8 and 86.4
+//                 64          32000 78.8 and 60.5, 64000 130.7 and 136.8
+// Beyond 65536 rows only instances whose lanes the columns fill keep up (1024
+// and 2048 columns; 1536 leave a quarter of them idle).  A union's partial
+// tiles cost the union kernel more: bound of 60432 rows, 3072 columns, 40
+// contexts 78.9 and 52.7; of 144656 rows 178.6 and 178.7.
+static bool two_groups_stream(int32_t K, int32_t B, int64_t rows, bool plan) {
+    if (K > 4096) return false;
+    if (K > 2048) return rows <= (plan ? 65536 : B > 40 ? 49152 : 24576);
+    const bool full = K > 1024 ? K >= 1792 : K >= 896;
+    return rows <= std::max<int64_t>(16384, full ? 128 * (int64_t)K : std::min<int64_t>(65536, 96 * (int64_t)K));
+}
+
 bool row_stream_eligible(const RowdotArgs& a) {
     if (a.wdtype != DYNA_BF16 || a.vdtype != DYNA_BF16 || a.K % 8 != 0 || a.K > 8192 || a.bias != nullptr ||
         a.act != DYNA_ACT_NONE || a.B < 1 || a.B > 64 || (a.vid_out != nullptr && a.perm == nullptr))
         return false;
-    const int64_t rows = a.plan.hdr != nullptr ? (int64_t)a.max_chunks_bound * kChunkRows : a.n_rows;
     if (a.B <= 16) return true;
-    return a.K <= 4096 && (a.B <= 32 || a.K <= 2048 || rows <= 65536);
+    if (a.B <= 32) return a.K <= 4096;
+    const bool plan = a.plan.hdr != nullptr;
+    return two_groups_stream(a.K, a.B, plan ? (int64_t)a.max_chunks_bound * kChunkRows : a.n_rows, plan);
 }
 
 dyna_status launch_row_stream(const RowdotArgs& a, hipStream_t stream) {

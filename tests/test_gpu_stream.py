@@ -52,6 +52,27 @@ def test_dense_rows_two_stages(rows, d):
     _check(head.logits.cpu(), W, h)
 
 
+def _close(got, W, h):
+    """_check on the GPU, in pieces of the rows."""
+    hd = h.to(DEV).double()
+    for r in range(0, W.shape[0], 8192):
+        w = W[r:r + 8192].to(DEV).double()
+        bound = (h.shape[1] / 4 + 64) * 2.0 ** -24 * (hd.abs() @ w.abs().T)
+        assert bool(((got[:, r:r + 8192].double() - hd @ w.T).abs() <= bound).all())
+
+
+# both sides of the lines between the row-streaming and the union kernel
+@pytest.mark.parametrize("rows,d,B", [(16384, 128, 40), (16385, 128, 40), (49152, 512, 33), (49153, 512, 33),
+                                      (24576, 4096, 40), (24577, 4096, 40), (49152, 3072, 41), (49153, 3072, 41),
+                                      (65536, 1536, 64), (65537, 1536, 64), (114688, 896, 50), (114689, 896, 50)])
+def test_dense_lines(rows, d, B):
+    W, h = _inputs(rows, d, B, rows)
+    head = D.DenseHead(W.to(DEV), rows, B, D.SEL_ARGMAX, 1, keep_logits=True)
+    head(h.to(DEV))
+    torch.cuda.synchronize()
+    _close(head.logits, W, h)
+
+
 def test_special_values_stay_in_their_row():
     """Infinities and NaN of one row (and of the last row, beside the tile's
     unused rows) reach that row's logits only; a context's columns past K
