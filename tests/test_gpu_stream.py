@@ -30,7 +30,7 @@ def _check(got, W, h):
 
 # K: one k step, ragged tails, each stage shape (up to 4, 8, 12, 16 steps per
 # wave, and two stages beyond 4096); B: both sides of every context group;
-# rows: one, around a tile, and several tiles per workgroup
+# rows: one, around a tile, and a few hundred tiles
 @pytest.mark.parametrize("d", [8, 40, 256, 1032, 2048, 3000, 4096])
 @pytest.mark.parametrize("B", [5, 16, 17, 32, 33, 64])
 @pytest.mark.parametrize("rows", [1, 16, 17, 4999])
@@ -52,6 +52,14 @@ def test_dense_rows_two_stages(rows, d):
     _check(head.logits.cpu(), W, h)
 
 
+# (d, B, tile sequences): every instance, k steps per wave of 4, 8, 12 and 16,
+# one and two stages, 16 and 32 contexts per workgroup, tiles shared by two
+# workgroups; the sequences are as many as the chip holds of that instance
+INSTANCES = [(1000, 16, 512), (1000, 32, 512), (1000, 64, 256), (2040, 13, 512), (2040, 29, 256), (2040, 57, 128),
+             (3000, 16, 256), (3000, 32, 256), (3000, 40, 128), (4096, 5, 256), (4096, 17, 256), (4096, 64, 128),
+             (6000, 16, 256), (8192, 9, 256)]
+
+
 def _close(got, W, h):
     """_check on the GPU, in pieces of the rows."""
     hd = h.to(DEV).double()
@@ -59,6 +67,18 @@ def _close(got, W, h):
         w = W[r:r + 8192].to(DEV).double()
         bound = (h.shape[1] / 4 + 64) * 2.0 ** -24 * (hd.abs() @ w.abs().T)
         assert bool(((got[:, r:r + 8192].double() - hd @ w.T).abs() <= bound).all())
+
+
+@pytest.mark.parametrize("d,B,seqs", INSTANCES)
+def test_dense_many_tiles(d, B, seqs):
+    """Three tiles and more for every workgroup, the last round partial and its
+    last tile ragged: registers, LDS and partial sums are used again and again."""
+    rows = 16 * (3 * seqs + 5) - 3
+    W, h = _inputs(rows, d, B, d + B)
+    head = D.DenseHead(W.to(DEV), rows, B, D.SEL_ARGMAX, 1, keep_logits=True)
+    head(h.to(DEV))
+    torch.cuda.synchronize()
+    _close(head.logits, W, h)
 
 
 # both sides of the lines between the row-streaming and the union kernel
@@ -110,3 +130,28 @@ def test_union_rows(B, d):
     _check(z, W[ids], h)
     top = np.argsort(-z.numpy(), axis=1, kind="stable")[:, :1]
     assert (head.ids.cpu().numpy()[:, :1] == ids[top]).all()
+
+
+@pytest.mark.parametrize("d,B,seqs", INSTANCES)
+def test_union_many_tiles(d, B, seqs):
+    """A union of more than three tiles per workgroup (chunks of 1-16 rows):
+    every slot's logit and every row's best ids, whose table the kernel wrote."""
+    rng = np.random.default_rng(B + d)
+    M, k, k_t = 37, 36, 4
+    V = 16 * 3 * seqs + 6000
+    sizes = rng.multinomial(V - 2 * M, np.full(M, 1.0 / M)) + 2
+    of = np.repeat(np.arange(M, dtype=np.int32), sizes)[rng.permutation(V)]
+    W, h = _inputs(V, d, B, 7 * B + d)
+    W1 = (torch.randn((M, d), generator=torch.Generator().manual_seed(1)) / d ** 0.5).to(torch.bfloat16)
+    L = D.build_layout(torch.from_numpy(of).to(DEV), W.to(DEV), M)
+    head = D.draft_head(D.Router(W1.to(DEV), act="none"), L, h.to(DEV), h.to(DEV), k,
+                        mode=D.SEL_TOPK | D.SEL_UNION, k_t=k_t)
+    torch.cuda.synchronize()
+    chosen = np.unique(head.clusters.cpu().numpy())
+    ids = np.concatenate([np.flatnonzero(of == m) for m in chosen])
+    assert sum(-(-int(sizes_m) // 16) for sizes_m in np.bincount(of, minlength=M)[chosen]) > 3 * seqs
+    _close(head.logits[:, :ids.size], W[ids], h)
+    z = head.logits[:, :ids.size].cpu().numpy()
+    for b in range(B):
+        best = np.lexsort((ids, -z[b]))[:k_t]
+        assert head.ids[b].cpu().tolist() == ids[best].tolist()
