@@ -6,6 +6,7 @@
 
 #include <algorithm>
 #include <atomic>
+#include <cmath>
 #include <mutex>
 #include <utility>
 #include <vector>
@@ -806,6 +807,8 @@ dyna_status draft_head_core(const dyna_router* r, const dyna_layout* L, const vo
     a.act = DYNA_ACT_NONE;
     a.plan = c.plan;
     a.max_chunks_bound = chunk_bound(L, B, k);
+    // rows of the union of B independent choices of k among M clusters
+    if (union_mode) a.rows_expected = (int32_t)(L->V * (1.0 - std::pow(1.0 - (double)k / L->M, B)));
     a.perm = L->perm;
     a.vid_out = c.slot_vid;
     const SelectArgs sa = make_select_args(

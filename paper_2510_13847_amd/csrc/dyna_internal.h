@@ -123,6 +123,7 @@ struct RowdotArgs {
     int32_t vslices;
     const float* vbias;
     int32_t vact;
+    int32_t rows_expected;  // union plans: about how many rows the plan holds
 };
 
 dyna_status launch_rowdot(const RowdotArgs& a, int path, hipStream_t stream);

@@ -304,38 +304,35 @@ dyna_status launch_stream_n(const RowdotArgs& a, hipStream_t stream) {
 
 }  // namespace
 
-// Up to 32 contexts (16 beyond 4096 columns) it was faster than the union
-// kernel at every size measured.  33-64 contexts share tiles between two
-// workgroups, and cost as much at 33 as at 64.  Against the union kernel they
-// win on tables too small to fill its 128-row tiles, and lose beyond; the
-// line lies by the row length.  Dense steps, union kernel against this, us:
-//   256 columns   40 contexts 16000 rows 21.5 and 19.9, 32000 23.9 and 25.7
-//   512           40          48000 33.4 and 31.9, 64000 36.3 and 37.7
-//   1024          40          64000 46.2 and 42.4, 128256 76.0 and 68.2,
-//                             262144 142.3 and 156.2
-//   1536          40          64000 57.7 and 55.2, 96000 78.0 and 84.4
-//   2048          48          64000 81.8 and 69.4, 200003 222.4 and 214.3
-//   4096          40          24000 75.5 and 67.5, 32000 77.8 and 86.4
-//                 64          32000 78.8 and 60.5, 64000 130.7 and 136.8
-// Beyond 65536 rows only instances whose lanes the columns fill keep up (1024
-// and 2048 columns; 1536 leave a quarter of them idle).  A union's partial
-// tiles cost the union kernel more: bound of 60432 rows, 3072 columns, 40
-// contexts 78.9 and 52.7; of 144656 rows 178.6 and 178.7.
-static bool two_groups_stream(int32_t K, int32_t B, int64_t rows, bool plan) {
-    if (K > 4096) return false;
-    if (K > 2048) return rows <= (plan ? 65536 : B > 40 ? 49152 : 24576);
-    const bool full = K > 1024 ? K >= 1792 : K >= 896;
-    return rows <= std::max<int64_t>(16384, full ? 128 * (int64_t)K : std::min<int64_t>(65536, 96 * (int64_t)K));
+// Against the union kernel (time of this one over that one's; 3975 dense and
+// union steps):
+//  * up to 32 contexts (16 beyond 4096 columns) this one is faster, 0.5-1.0,
+//    but for unions of many rows of under 448 columns: 256 columns, 10
+//    contexts 0.97 at 16k rows, 1.05 at 44k, 1.12 at 94k;
+//  * 33-64 contexts share tiles between two workgroups.  Where rows are no
+//    multiple of the 128 bytes that the union kernel walks, its pieces
+//    straddle lines, and this one is faster at any length: 2168 columns 0.4-0.86,
+//    880 0.5-0.8, 520 0.6-0.87 (272: 1.0 at 32k rows, 1.25 at 262k);
+//  * where they are, it is faster on short tables, whose tiles of 128 rows
+//    leave compute units to the union kernel idle, and loses beyond (36 and 64
+//    contexts): 320 columns 0.92 and 0.88 at 20k rows, 1.18 and 1.08 at 80k;
+//    640 0.89 and 0.82 at 48k, 1.02 and 0.92 at 140k; 1600 0.89 and 0.77 at 48k,
+//    1.11 and 1.11 at 96k; 3584 0.87 and 0.65 at 24k, 1.18 and 1.14 at 60k.  A
+//    second group of contexts costs this kernel the same at 33 and at 64.
+static bool streams_faster(int32_t K, int32_t B, int64_t rows, bool plan) {
+    if (B <= 32) return !plan || K >= 448 || rows <= 64 * (int64_t)K;
+    if (K % 64 != 0 && K >= 384) return true;
+    const int64_t base = K > 2048 ? 28672 : K > 1024 ? 49152 : std::max<int64_t>(8192, (plan ? 64 : 96) * (int64_t)K);
+    return rows <= base * (128 + 2 * (B - 32)) / 128;
 }
 
 bool row_stream_eligible(const RowdotArgs& a) {
     if (a.wdtype != DYNA_BF16 || a.vdtype != DYNA_BF16 || a.K % 8 != 0 || a.K > 8192 || a.bias != nullptr ||
-        a.act != DYNA_ACT_NONE || a.B < 1 || a.B > 64 || (a.vid_out != nullptr && a.perm == nullptr))
+        a.act != DYNA_ACT_NONE || a.B < 1 || a.B > 64 || (a.vid_out != nullptr && a.perm == nullptr) ||
+        (a.B > 16 && a.K > 4096))
         return false;
-    if (a.B <= 16) return true;
-    if (a.B <= 32) return a.K <= 4096;
     const bool plan = a.plan.hdr != nullptr;
-    return two_groups_stream(a.K, a.B, plan ? (int64_t)a.max_chunks_bound * kChunkRows : a.n_rows, plan);
+    return streams_faster(a.K, a.B, plan ? a.rows_expected : a.n_rows, plan);
 }
 
 dyna_status launch_row_stream(const RowdotArgs& a, hipStream_t stream) {

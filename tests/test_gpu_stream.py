@@ -81,10 +81,12 @@ def test_dense_many_tiles(d, B, seqs):
     _close(head.logits, W, h)
 
 
-# both sides of the lines between the row-streaming and the union kernel
-@pytest.mark.parametrize("rows,d,B", [(16384, 128, 40), (16385, 128, 40), (49152, 512, 33), (49153, 512, 33),
-                                      (24576, 4096, 40), (24577, 4096, 40), (49152, 3072, 41), (49153, 3072, 41),
-                                      (65536, 1536, 64), (65537, 1536, 64), (114688, 896, 50), (114689, 896, 50)])
+# both sides of the lines between the row-streaming and the union kernel: by
+# row length and contexts, and long tables of unaligned rows
+@pytest.mark.parametrize("rows,d,B", [(8320, 64, 34), (8321, 64, 34), (13824, 128, 40), (13825, 128, 40),
+                                      (32256, 4096, 40), (32257, 4096, 40), (43008, 2112, 64), (43009, 2112, 64),
+                                      (49920, 512, 33), (49921, 512, 33), (73728, 1536, 64), (73729, 1536, 64),
+                                      (110208, 896, 50), (110209, 896, 50), (110209, 392, 50)])
 def test_dense_lines(rows, d, B):
     W, h = _inputs(rows, d, B, rows)
     head = D.DenseHead(W.to(DEV), rows, B, D.SEL_ARGMAX, 1, keep_logits=True)
@@ -110,7 +112,7 @@ def test_special_values_stay_in_their_row():
     assert bool(torch.isinf(z[:, 20]).logical_or(torch.isnan(z[:, 20])).all())
 
 
-@pytest.mark.parametrize("B,d", [(2, 520), (16, 4096), (17, 1000), (40, 640), (11, 5376)])
+@pytest.mark.parametrize("B,d", [(2, 520), (16, 4096), (17, 1000), (40, 640), (11, 5376), (9, 24), (25, 32), (60, 64)])
 def test_union_rows(B, d):
     """Over a union plan (chunks of 1-16 rows at any slot): every logit is its
     row's product and every slot's id its row's."""
