@@ -18,7 +18,7 @@ constexpr int kCountThreads = 1024;
 constexpr size_t kCountLds = 128 * 1024;  // budget of the per-wave counters
 
 // Waves of a counting workgroup: as many as have 16-bit counters for every
-// cluster within the LDS budget (4 at 16384 clusters).
+// cluster within the LDS budget (16 up to 4096 clusters, 8 up to 8192).
 int count_waves(int32_t M) {
     int w = kCountThreads / kWave;
     while (w > 1 && (size_t)w * (size_t)M * 2 > kCountLds) w >>= 1;

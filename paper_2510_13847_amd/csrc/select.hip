@@ -711,8 +711,8 @@ dyna_status launch_topk_clusters(const float* scores, int32_t B, int32_t M, int3
     // four to eight scores per thread: 4096 clusters (128 contexts) 18.9 us
     // with 256 threads, 13.2 with 1024; 2048 (16 contexts) 12.5 with 256,
     // 11.1 with 512; at 1024 clusters more threads lose to their barriers
-    // (more waves also take a few more bytes of static LDS; near the 160 KiB
-    // limit, about 10000 clusters, 256 threads still fit where 1024 would not)
+    // (more waves also take a few more bytes of static LDS; at the 160 KiB limit,
+    // 8192 clusters and k from 1915 to 1917, 256 threads fit where 1024 do not)
     if (M <= 1024 || lds > 156 * 1024) return launch(std::integral_constant<int, 256>{});
     if (M <= 2048) return launch(std::integral_constant<int, 512>{});
     return launch(std::integral_constant<int, 1024>{});

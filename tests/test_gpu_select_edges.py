@@ -178,3 +178,20 @@ def test_long_row_top_kt(n, kind, k_t):
         lp = out["logprobs"].cpu().numpy()[0, :len(order)]
         # fp32: at most 64 terms per thread, a tree over 1024 threads, one logarithm
         assert np.abs(lp[fin] - ref[fin]).max() <= 1e-5 * max(1.0, np.abs(ref[fin]).max())
+
+
+# the k best clusters at the edges of the workgroup sizes (1024 and 2048
+# clusters) and, at the most clusters, of the LDS budget: from k = 1792 on 256
+# threads run, and up to k = 1917 only they fit
+@pytest.mark.parametrize("M,k", [(1024, 64), (1025, 1025), (2048, 7), (2049, 2049), (8192, 1), (8192, 1791),
+                                 (8192, 1792), (8192, 1917)])
+def test_top_clusters(M, k):
+    g = torch.Generator().manual_seed(M + k)
+    W1 = torch.randint(-4, 5, (M, 8), generator=g).to(torch.bfloat16)  # (few distinct scores: many ties)
+    x = torch.randint(-4, 5, (3, 8), generator=g).to(torch.bfloat16)
+    ids, sc, scores = D.route(D.Router(W1.to(DEV), act="none"), x.to(DEV), k, want_scores=True)
+    s = (x.float() @ W1.float().T).numpy()
+    assert (scores.cpu().numpy() == s).all()
+    for b in range(3):
+        order = np.lexsort((np.arange(M), -s[b]))[:k]
+        assert ids[b].cpu().tolist() == order.tolist() and sc[b].cpu().tolist() == s[b][order].tolist()
