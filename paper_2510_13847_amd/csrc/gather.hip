@@ -766,11 +766,11 @@ dyna_status launch_union_nt(const RowdotArgs& a, int cfg, hipStream_t stream) {
             if constexpr (NT >= 8) return launch_union_cfg<8, 2, 64, NT>(a, stream);
             else if constexpr (NT == 4) return launch_union_cfg<8, 1, 64, NT, 3>(a, stream);
             else if constexpr (NT == 2) return launch_union_cfg<4, 1, 64, NT, 3>(a, stream);
-            // up to 16 contexts (rows beyond the row-streaming kernel's 8192
-            // columns): two-wave workgroups of 64-column stages (many small
-            // workgroups per CU).  Measured at ten contexts over 31.6k rows:
-            // 52.2 us against 60.3 with 128-column stages and 54-81 us for
-            // deeper rings or more rows per wave
+            // up to 16 contexts (long unions of short rows): two-wave workgroups
+            // of 64-column stages (many small workgroups per CU).  Measured at
+            // ten contexts over 31.6k rows of 4096 columns: 52.2 us against 60.3
+            // with 128-column stages and 54-81 us for deeper rings or more rows
+            // per wave
             else return launch_union_cfg<2, 1, 64, NT, 3>(a, stream);
     }
 }
@@ -798,9 +798,11 @@ dyna_status launch_gather_lds(const RowdotArgs& a, hipStream_t stream) {
         case 9: return launch_ring_cfg<8, 4, 128, 8>(a, stream);
         default:
             // a short shortlist (at most a few thousand chunks): four waves
-            // split each chunk's k dimension.  Measured at ten contexts: 19.0
-            // -> 17.2 us over 5.9k rows, 26.0 -> 23.4 us over 9.2k rows; the
-            // other split shapes gained less or lost.
+            // split each chunk's k dimension.  Steps of 33-96 contexts, unsplit
+            // and split: 8192 x 2048 rows, 8 clusters each 46.5 and 44.2 us (64
+            // contexts), 55.5 and 51.4 (96); 32768 x 4096, 4 clusters 59.6 and
+            // 56.6 (64); up to the line (50021 x 1736, 21 clusters) 59.8 and 59.9
+            // (33), 71.2 and 69.1 (64), 77.6 and 80.1 (96).
             if (a.max_chunks_bound <= kSplitChunks) return launch_ring_cfg<4, 4, 128, 4>(a, stream);
             return launch_ring_cfg<2, 4, 256>(a, stream);  // two workgroups of two waves per CU
     }
@@ -827,10 +829,7 @@ dyna_status launch_union_argmax(const RowdotArgs& a, int cfg, hipStream_t stream
         case 5: return launch_union_cfg<4, 4, 64, 8, 3, 1>(a, stream);
         case 6: return launch_union_cfg<8, 2, 64, 8, 0, 1>(a, stream);
         case 7: return launch_union_cfg<8, 4, 64, 8, 2, 1>(a, stream);
-        // eight waves of two row tiles (256 rows) against 256 centroids,
-        // double-buffered (two 64 KB stages): the fastest of these shapes,
-        // 1292 us where the nearest-centroid kernel takes 835
-        default: return launch_union_cfg<8, 2, 64, 16, 2, 1>(a, stream);
+        default: return set_error(DYNA_ERR_UNSUPPORTED, "nearest centroid: no fixed shape %d", cfg);
     }
 }
 
