@@ -465,7 +465,7 @@ def bench_kmeans(w, args, D, torch):
         "higher_is_better": True, "scaling": "weak", "vs_baseline": None,
         "dtype": "bf16", "data": "synthetic",
         "config": {"workload": f"{w.name} LM head, spherical k-means", "V": w.V, "d": w.d, "M": w.M,
-                   "rounds": R, "timing": "one dyna_kmeans call (row norms, initial centroids, rounds, final sync)"},
+                   "rounds": R, "timing": "one dyna_kmeans call (initial centroids, rounds, final sync)"},
         "cluster_sizes": {"min": int(sizes.min()), "max": int(sizes.max()), "empty": int((sizes == 0).sum())},
         "roofline": {"kernel": "k-means assignment: every row against every centroid on the matrix cores, argmax epilogue",
                      "kernel_symbol": "nearest_centroid_kernel", "bound": "mfma",

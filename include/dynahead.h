@@ -417,14 +417,15 @@ int32_t dyna_static_budget(int32_t t, int32_t k_max);
  *   0 automatic (256), else 1..4096; of the one-launch step: 0 automatic (one
  *   per compute unit), else that many, capped at 1024 and at what the
  *   occupancy calculator says can be resident at once.
- * DYNA_OPT_UNION_CFG: shape of the dense union-row kernel of
- *   DYNA_SEL_UNION steps: 0 automatic (up to 16 rows over a row stride of at
- *   most 65536 slots take the per-chunk gathered kernel instead), 1..15
- *   fixed (waves per workgroup, row tiles per wave, k columns per stage, ring
- *   depth; always the dense kernel); a shape whose ring does not fit in LDS
+ * DYNA_OPT_UNION_CFG: kernel of the dense products of several bf16 contexts,
+ *   DYNA_SEL_UNION steps and dyna_dense_head with more than 4 contexts: 0
+ *   automatic (the row-streaming kernel where it is the faster one by
+ *   contexts, row length and rows, else the union kernel), 1..15 the union
+ *   kernel in a fixed shape (waves per workgroup, row tiles per wave, k
+ *   columns per stage, ring depth); a shape whose ring does not fit in LDS
  *   for the batch's context count returns DYNA_ERR_UNSUPPORTED.
- * DYNA_OPT_KMEANS_CFG: shape of the k-means assignment kernel: 0
- *   automatic, 1..7 fixed.
+ * DYNA_OPT_KMEANS_CFG: kernel of the k-means assignment: 0 automatic (the
+ *   nearest-centroid kernel), 1..7 fixed shapes of the union kernel.
  * DYNA_OPT_WAIT_BOUND_US: bound of every wait of the one-launch step, in
  *   microseconds of wall clock: 0 (default) 200000, 1..1000000 that many,
  *   -1 none (a wait gives up at its first read that finds a word missing;

@@ -395,9 +395,10 @@ static dyna_status run_router(const dyna_router* r, const void* x, int32_t xdtyp
 // Path of a gathered head with per-row shortlists: the option when set, else
 // the wave-per-row GEMV for up to 32 contexts and the LDS-staged MFMA tiles
 // beyond.  The GEMV's 1 KiB row loads stream better when a slab row serves
-// few contexts: measured 4-12 us less per step at 8-48 contexts on the
-// Llama-3-8B head and 6-7 us at 16 contexts on the Qwen- and Gemma-shaped
-// heads; equal at 32 and 32 us more at 64 contexts on the Gemma-shaped head.
+// few contexts.  Steps, GEMV and MFMA, us: Llama-3-8B head 16 contexts 97.1 and
+// 105.1, 32 128.4 and 137.2, 64 175.7 and 181.2; Qwen-shaped 16 100.4 and
+// 106.7, 32 138.2 and 141.7, 48 168.1 and 165.4, 64 195.9 and 186.3;
+// Gemma-shaped 16 142.2 and 147.9, 32 218.0 and 215.2, 64 334.8 and 302.6.
 constexpr int32_t kGemvMaxContexts = 32;
 static int gathered_path(int32_t B) {
     const int opt = option_logits_path();
@@ -774,8 +775,8 @@ dyna_status draft_head_core(const dyna_router* r, const dyna_layout* L, const vo
     TRY(run_router(r, x, adtype, B, c.scores, c.hidden, c.rpart, c.rpart_floats, rs, fused ? c.counters : nullptr,
                    B > 1 ? &slices : nullptr));
     // union rows: one dense product of the union's slabs with every context
-    // (it needs only one list entry per union cluster, and writes one shared
-    // copy of the slots' vocabulary ids)
+    // (its plan needs no lists, and it writes one shared copy of the slots'
+    // vocabulary ids)
     const bool dense_union = union_mode && option_logits_path() == 0 && L->wdtype == DYNA_BF16 &&
                              adtype == DYNA_BF16 && L->d % 8 == 0;
     if (union_mode) {
@@ -822,11 +823,13 @@ dyna_status draft_head_core(const dyna_router* r, const dyna_layout* L, const vo
         TRY(timed([&] { return dense_rows_stream(a) ? launch_row_stream(a, stream) : launch_union_gemm(a, stream); },
                   stream));
     else TRY(timed_rowdot(a, union_mode ? option_logits_path() : gathered_path(B), stream));
-    // union rows over a few thousand slots select faster in one launch (one
-    // workgroup per row); long union rows split into segments.  Measured at
-    // ten rows: 6-7 us saved per step at unions of 3.7-5.9k slots (row
-    // strides up to 26k), 3 us lost at 9.2k (stride 39k), 28 us at 32k; 77 us
-    // lost at 64 rows of 32k.
+    // union rows select in one launch (one workgroup per row) or, long ones, in
+    // segments.  The line is their length, 16384 slots: one launch and segments
+    // over 128256 x 2048 rows, ten rows of 4.6k slots 37.9 and 41.9 us, 9.6k 41.8
+    // and 44.6, 17.8k 64.7 and 51.0, sixteen of 15.1k 48.8 and 50.4.  The host
+    // knows the stride, a bound: rows of strides up to 32768 are mostly shorter
+    // than the line, of longer strides mostly longer (where they are not, 5-13%
+    // are left: ten rows of 4.9k slots 43200 apart 40.3 and 44.9).
     constexpr int32_t kUnionSplitCap = 32768;
     return launch_select(logits, cap, c.row_len, 0, cap, c.sel_sorted, c.sel_rowoff, L->offsets, L->perm, B,
                          k, k_t, temperature, tail_beta, L->V, want_sample ? uniforms : nullptr,
