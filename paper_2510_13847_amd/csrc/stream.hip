@@ -307,12 +307,16 @@ dyna_status launch_stream_n(const RowdotArgs& a, hipStream_t stream) {
 // Against the union kernel (time of this one over that one's; 3975 dense and
 // union steps):
 //  * up to 32 contexts (16 beyond 4096 columns) this one is faster, 0.5-1.0,
-//    but for unions of many rows of under 448 columns: 256 columns, 10
-//    contexts 0.97 at 16k rows, 1.05 at 44k, 1.12 at 94k;
+//    but for unions of many short rows, whose tiles it hands out in tasks of a
+//    few KB: 256 columns, 10 contexts 0.97 at 16k rows, 1.05 at 44k, 1.12 at 94k;
+//    320 columns 1.00-1.11, 384 1.00-1.06, 448 1.0.  Rows that are no multiple
+//    of 128 bytes (next item) turn earlier: 264 columns 0.95-1.06, 296
+//    0.93-1.05, 328 0.89-1.04, 392 0.86-1.01 (60k-250k rows, 3-28 contexts);
 //  * 33-64 contexts share tiles between two workgroups.  Where rows are no
 //    multiple of the 128 bytes that the union kernel walks, its pieces
 //    straddle lines, and this one is faster at any length: 2168 columns 0.4-0.86,
-//    880 0.5-0.8, 520 0.6-0.87 (272: 1.0 at 32k rows, 1.25 at 262k);
+//    880 0.5-0.8, 520 0.6-0.87, 328-376 0.87-1.06 (272: 1.0 at 32k rows, 1.25 at
+//    262k);
 //  * where they are, it is faster on short tables, whose tiles of 128 rows
 //    leave compute units to the union kernel idle, and loses beyond (36 and 64
 //    contexts): 320 columns 0.92 and 0.88 at 20k rows, 1.18 and 1.08 at 80k;
@@ -320,8 +324,9 @@ dyna_status launch_stream_n(const RowdotArgs& a, hipStream_t stream) {
 //    1.11 and 1.11 at 96k; 3584 0.87 and 0.65 at 24k, 1.18 and 1.14 at 60k.  A
 //    second group of contexts costs this kernel the same at 33 and at 64.
 static bool streams_faster(int32_t K, int32_t B, int64_t rows, bool plan) {
-    if (B <= 32) return !plan || K >= 448 || rows <= 64 * (int64_t)K;
-    if (K % 64 != 0 && K >= 384) return true;
+    const bool straddles = K % 64 != 0;
+    if (B <= 32) return !plan || K >= (straddles ? 288 : 448) || rows <= 64 * (int64_t)K;
+    if (straddles && K >= 320) return true;
     const int64_t base = K > 2048 ? 28672 : K > 1024 ? 49152 : std::max<int64_t>(8192, (plan ? 64 : 96) * (int64_t)K);
     return rows <= base * (128 + 2 * (B - 32)) / 128;
 }

@@ -86,13 +86,32 @@ def test_dense_many_tiles(d, B, seqs):
 @pytest.mark.parametrize("rows,d,B", [(8320, 64, 34), (8321, 64, 34), (13824, 128, 40), (13825, 128, 40),
                                       (32256, 4096, 40), (32257, 4096, 40), (43008, 2112, 64), (43009, 2112, 64),
                                       (49920, 512, 33), (49921, 512, 33), (73728, 1536, 64), (73729, 1536, 64),
-                                      (110208, 896, 50), (110209, 896, 50), (110209, 392, 50)])
+                                      (110208, 896, 50), (110209, 896, 50), (110209, 392, 50),
+                                      (98000, 312, 40), (98000, 328, 40)])
 def test_dense_lines(rows, d, B):
     W, h = _inputs(rows, d, B, rows)
     head = D.DenseHead(W.to(DEV), rows, B, D.SEL_ARGMAX, 1, keep_logits=True)
     head(h.to(DEV))
     torch.cuda.synchronize()
     _close(head.logits, W, h)
+
+
+@pytest.mark.parametrize("B,d", [(3, 280), (29, 280), (3, 288), (29, 296), (16, 384), (16, 392), (16, 440), (16, 448)])
+def test_union_lines(B, d):
+    """Unions of more than 64 rows per column: short aligned rows take the
+    union kernel, the others the row-streaming one."""
+    M = 32
+    V = 64 * d + 2000
+    of = torch.arange(V, dtype=torch.int32) % M
+    W, h = _inputs(V, d, B, B + d)
+    W1 = (torch.randn((M, d), generator=torch.Generator().manual_seed(1)) / d ** 0.5).to(torch.bfloat16)
+    L = D.build_layout(of.to(DEV), W.to(DEV), M)
+    head = D.draft_head(D.Router(W1.to(DEV), act="none"), L, h.to(DEV), h.to(DEV), M,
+                        mode=D.SEL_TOPK | D.SEL_UNION, k_t=1)
+    torch.cuda.synchronize()
+    ids = torch.arange(V).reshape(-1, 1)[torch.argsort(of, stable=True)].flatten()
+    _close(head.logits[:, :V], W[ids], h)
+    assert head.ids[:, 0].cpu().tolist() == ids[head.logits[:, :V].argmax(1).cpu()].tolist()
 
 
 def test_special_values_stay_in_their_row():
