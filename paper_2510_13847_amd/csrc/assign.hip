@@ -24,10 +24,10 @@
 //    one 64-bit maximum per row, (value, lower id), whose result does not
 //    depend on the order.
 //
-// Measured, 128256 x 4096 rows against 1024 centroids (1.08 TFLOP): 1292 ->
-// 835 us on rows with cluster structure (1.29 PFLOP/s) and 1419 -> 968 us on
-// random ones, where the chip's power holds the clock lower; a library GEMM
-// of this shape, which also writes its 263 MB result, 936 us.  Steps on the
+// Measured, 128256 x 4096 rows against 1024 centroids (1.08 TFLOP), by card:
+// 1292 -> 835-863 us on rows with cluster structure (1.25-1.29 PFLOP/s) and
+// 1349-1419 -> 864-968 us on random ones; a library GEMM of this shape, which
+// also writes its 263 MB result, 936 us.  Steps on the
 // way (random rows): both operands two stages deep 1118 us, three stages of
 // rows 1047, loads between the products 1017, reads between them too 1002.
 // Without the loads the products alone take 790 us.
